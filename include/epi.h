@@ -302,9 +302,9 @@ int epi_batch_destroy(epi_ctx *ctx, int32_t batch_id);
  *            4 n_cases + 2^T n_controls < 2^24 (e.g. up to 2047 individuals
  *            per class).
  * Every kernel produces the same integers and therefore the same results.
- * Plain scans on the matrix-core blocks with at least 64 work items per wave
- * first run a pilot pass: one work item per wave, from the middle of the
- * scan, whose best screening sums, lowered by the screen's error bound, go
+ * Scans of order 2, of order 3 on the matrix-core blocks and of order 4 by
+ * reduced cells first run a pilot pass: up to one work item per wave, from
+ * the middle of the scan, whose best screening sums, lowered by the screen's error bound, go
  * into the scan's score histogram; the K-th best of those is a lower bound
  * of the final K-th best score, which every wave of the scan then starts
  * from (same results, fewer combinations scored exactly while the bound

@@ -159,6 +159,28 @@ EPI_DEV long long hist_bound(const unsigned *h, int K, int top) {
     return (long long)0x8000000000000000ull;
 }
 
+// The same over the whole histogram: each lane sums one leading-bit position
+// (highest first), then the wave looks inside the one where the sum reaches K.
+EPI_DEV long long hist_bound_all(const unsigned *h, int K) {
+    const int lane = lane_id(), oct = 63 - lane;
+    unsigned s = 0;
+    if (oct < 63) {  // position 63 is never counted (its last word is the pilot counter)
+        #pragma unroll
+        for (int b = 0; b < kHistFine; ++b)
+            s += __hip_atomic_load(h + oct * kHistFine + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const unsigned cs = wave_scan_incl(s);
+    const unsigned long long m = __ballot(cs >= (unsigned)K);
+    if (!m) return (long long)0x8000000000000000ull;
+    const int src = (int)__builtin_ctzll(m);
+    const unsigned above = (unsigned)__builtin_amdgcn_readlane((int)(cs - s), src);
+    const int top = (63 - src) * kHistFine + kHistFine - 1;
+    const unsigned c =
+        lane < kHistFine ? __hip_atomic_load(h + top - lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    const unsigned long long m2 = __ballot(wave_scan_incl(c) + above >= (unsigned)K);
+    return m2 ? hist_edge(top - (int)__builtin_ctzll(m2)) : hist_edge(top - kHistFine + 1);
+}
+
 // Rank of pair (x, y), x < y, in the lexicographic order of the pairs of M.
 EPI_DEV unsigned long long lexpair(long long x, long long y, long long M) {
     return (unsigned long long)(x * (2 * M - x - 1) / 2 + (y - x - 1));
@@ -612,19 +634,23 @@ EPI_DEV long long entry_bound(const TopK &tk, long long gthr) {
 }
 
 // Pilot pass over an item: the wave's best screening sum S (best over its
-// lanes' combinations; INT_MIN: none) becomes one histogram count.  S is
-// within `reads` units (2^-tq) of (num - score_const) 2^(tq - shift) (each
-// table value within one unit of its n ln n, as in screen_bound), so
-// score_const + (S - reads - 1) 2^(shift - tq) is below that combination's
-// num; one atomic per wave, and the K-th best of such maxima is close to the
-// K-th best of all the item's combinations.
+// lanes' combinations; INT_MIN: none) becomes one histogram count, or each
+// lane's best one count where the task has too few pilot items for K counts
+// (pilot_lanes).  S is within `reads` units (2^-tq) of (num - score_const)
+// 2^(tq - shift) (each table value within one unit of its n ln n, as in
+// screen_bound), so score_const + (S - reads - 1) 2^(shift - tq) is below
+// that combination's num; one atomic per wave, and the K-th best of such
+// maxima is close to the K-th best of all the item's combinations.
 EPI_DEV void pilot_count(TopK &tk, const Task &t, int best, int reads) {
-    #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const int o = __shfl_xor(best, off);
-        best = o > best ? o : best;
+    const bool lanes = t.pilot_lanes != 0;
+    if (!lanes) {
+        #pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const int o = __shfl_xor(best, off);
+            best = o > best ? o : best;
+        }
     }
-    hist_add(tk, lane_id() == 0 && best != (int)0x80000000u,
+    hist_add(tk, (lanes || lane_id() == 0) && best != (int)0x80000000u,
              t.score_const + (long long)(best - reads - 1) * (1ll << (t.ds.shift - t.ds.tq)));
 }
 
@@ -2347,15 +2373,14 @@ scan_pilot(const Task *__restrict__ tasks, int n_tasks, unsigned long long total
                 else item_f3m<true, false, i8, false, false, nj, true>(T, local, tk, s_list, none, s_stage);
             }
         }
-        // the task's last pilot wave takes the bound (from one octave above
-        // its own count down)
+        // the task's last pilot wave takes the bound
         __threadfence();
         unsigned prev = 0;
         if (lane_id() == 0) prev = atomicAdd(T.hist + kPilotWord, 1u);
         prev = (unsigned)__builtin_amdgcn_readfirstlane((int)prev);
-        if (prev + 1 == (unsigned)T.pilot_n && tk.top >= 0) {
+        if (prev + 1 == (unsigned)T.pilot_n) {
             __threadfence();
-            const long long hb = hist_bound(T.hist, T.top_k, tk.top);
+            const long long hb = hist_bound_all(T.hist, T.top_k);
             if (hb != none && lane_id() == 0) atomicMax(T.thr, bias(hb));
         }
     }

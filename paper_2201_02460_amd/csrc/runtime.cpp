@@ -644,10 +644,29 @@ int default_np3(Ctx *c, const Dataset *d) {
     return d->qa ? kNpMfma : 4;
 }
 
+// The pilot pass pays as soon as a scan's waves would otherwise fill their
+// lists from nothing: without a bound nearly every combination is scored
+// exactly and offered (order 3, M = 151, N = 1237, K = 50: 894 us a scan
+// without, 178 with; M = 200, N = 2000, K = 100: 1503 and 273).  Its items
+// are counted twice, so it takes 1/32 of the scan (1/16 cost M = 461,
+// N = 7086 0.5 %), or 4 K items where that is more, and at most one item per
+// wave, which large scans reach.  An order-2 scan whose items all run at once has only a few hundred
+// pairs per wave to save, so there the second counting must be short: M = 298
+// at N = 4000 takes 166 us without and 156 with, at N = 9483 152 and 162.
 int pilot_items_for(int variant, int np, unsigned long long n_items, int top_k, int N, int tab_cap, int waves) {
     if (!((variant == kF3 && is_mfma_np(np)) || variant == kR4 || variant == kF2) || tab_cap < N + 1) return 0;
-    const unsigned long long n = std::min<unsigned long long>((unsigned long long)waves, n_items / 32) & ~3ull;
-    return n >= 2ull * (unsigned long long)std::max(top_k, 1) ? (int)n : 0;
+    if (variant == kF2 && n_items <= (unsigned long long)waves && N > 6000) return 0;
+    const unsigned long long want = std::max<unsigned long long>(n_items / 32, 4ull * std::max(top_k, 1));
+    const unsigned long long n = std::min({(unsigned long long)waves, n_items, want});
+    return (int)((n + 3) & ~3ull);
+}
+
+// The task's pilot fields for pilot_n items out of n_items.
+void set_pilot(Task &t, int pilot_n, unsigned long long n_items) {
+    t.pilot_n = pilot_n;
+    t.pilot_first = n_items > (unsigned long long)pilot_n ? (n_items - (unsigned long long)pilot_n) / 2 : 0;
+    t.pilot_lanes = pilot_n < 4 * t.top_k ? 1 : 0;
+    t.pilot_base = 0;
 }
 
 int group_list_cap(int np2, int np3, int gk, int tab_cap, int top_k, int stage_cap) {
@@ -1036,14 +1055,10 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
         t.digest = check ? p->d_digest + 2 * i : nullptr;
         // pilot pass: consecutive items from the middle of the task
         s.pilot_n = 0;
-        s.pilot_first = 0;
         for (const LaunchGroup &g : p->groups)
             if (std::find(g.scans.begin(), g.scans.end(), i) != g.scans.end())
                 s.pilot_n = pilot_items_for(s.variant, s.np, s.n_items, s.desc.top_k, s.ds->N, g.tab_cap, g.grid * 4);
-        s.pilot_first = (s.n_items - (unsigned long long)s.pilot_n) / 2;
-        t.pilot_first = s.pilot_first;
-        t.pilot_n = s.pilot_n;
-        t.pilot_base = 0;
+        set_pilot(t, s.pilot_n, s.n_items);
     }
     {
         int e = nt;
@@ -1056,9 +1071,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
             t = tasks[i];
             t.variant = kF2Emit;
             t.digest = nullptr;
-            t.pilot_first = 0;
-            t.pilot_n = 0;
-            t.pilot_base = 0;
+            set_pilot(t, 0, 0);
             t.items = (const unsigned long long *)s.emit_items_d;
             t.n_items = s.emit_items;
             t.item_base = persistent ? base : 0;
@@ -1092,9 +1105,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
             t = tasks[i];
             t.variant = kF3Emit;
             t.digest = nullptr;
-            t.pilot_first = 0;
-            t.pilot_n = 0;
-            t.pilot_base = 0;
+            set_pilot(t, 0, 0);
             t.items = (const unsigned long long *)s.t3_items_d;
             t.n_items = s.t3_items;
             t.item_base = persistent ? base : 0;

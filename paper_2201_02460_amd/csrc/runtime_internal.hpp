@@ -83,10 +83,8 @@ struct PlanScan {
     unsigned cand_cap = 0;
     ResultLayout lay{};
     int scan_id = -1;
-    // matrix-core order 3 and reduced-cell order 4: pilot pass over items
-    // pilot_first .. pilot_first + pilot_n - 1 (pilot_n 0: none)
+    // pilot pass over pilot_n items from the middle of the scan (0: none)
     int pilot_n = 0;
-    unsigned long long pilot_first = 0;
 };
 
 struct LaunchGroup {
@@ -197,11 +195,10 @@ struct Ctx {
 hipError_t launch_pilot(int np2, int np3, int gk, int grid, hipStream_t st, const Task *tasks, int n_tasks,
                         unsigned long long total, const unsigned long long *binom, int bstride, int tab_cap, int kmax,
                         int stage_cap);
-// Pilot items of a task (a multiple of 4; 0: none): up to one per wave of its
-// launch, when the task has at least 32 items per pilot item and the pilot
-// counts can reach a bound (twice top_k of them), and its screening table
+// Pilot items of a task (a multiple of 4; 0: none), when its screening table
 // fits the launch's LDS table (tab_cap entries).
 int pilot_items_for(int variant, int np, unsigned long long n_items, int top_k, int N, int tab_cap, int waves);
+void set_pilot(Task &t, int pilot_n, unsigned long long n_items);
 // 4-wave workgroups per CU of a scan kernel instantiation (VGPRs and LDS:
 // screening-table entries, best-K list entries per wave, staged rows).
 int wgs_per_cu(int np2, int np3, int gk, int tab_cap, int kmax, int stage_cap);

@@ -40,10 +40,9 @@ struct Request {
     unsigned long long n_items = 0, cursor = 0, emit_n = 0, t3_n = 0, n_combos = 0;
     bool emit_done = false;
     bool finishing = false;  // its last slice is in the round in flight (results not yet read)
-    // pilot pass in the request's first round (matrix-core order 3, order 4
-    // by reduced cells): items pilot_first .. + pilot_n - 1
+    // pilot pass in the request's first round: pilot_n items from the middle
+    // of its scan
     int pilot_n = 0;
-    unsigned long long pilot_first = 0;
     bool big_tab = false;  // its screening table lowers the kernel's workgroups per CU
     void *pairs = nullptr, *triples = nullptr, *cand = nullptr;
     unsigned cand_cap = 0;
@@ -165,7 +164,6 @@ static int admit(Server *S, Request *r) {
     r->pilot_n = pilot_items_for(r->variant, r->np, r->n_items, r->desc.top_k, r->ds->N, Plan::kTabMax,
                                  S->grid_max * 4);
     r->big_tab = table_lowers_occupancy(r->ds, r->variant, r->np, o, r->desc.top_k);
-    r->pilot_first = (r->n_items - (unsigned long long)r->pilot_n) / 2;
     const uint64_t pair_bytes = sub ? pair_table_bytes(r->variant, r->ds->M) : 0;
     const uint64_t trip_bytes = r->variant == kR4 ? triple_table_bytes(r->ds->M) : 0;
     r->footprint = pair_bytes + trip_bytes + (uint64_t)r->cand_cap * sizeof(Cand);
@@ -207,8 +205,7 @@ static Task make_task(Server *S, Request *r) {
     t.top_k = r->desc.top_k;
     t.np = r->np;
     t.key_bits = key_bits_for(r->desc.order);
-    t.pilot_first = r->pilot_first;
-    t.pilot_n = r->pilot_n;
+    set_pilot(t, r->pilot_n, r->n_items);
     return t;
 }
 
