@@ -242,15 +242,17 @@ def orders_bench(epi, torch, names, steps):
         epi.epi_unload(ctx, ds)
         kms = sorted(mains)[len(mains) // 2]
         # reduced-cell variants count 2^k cells, the generic one all 3^k;
-        # order 2 may run on the matrix cores (2 x 2^2 flops per unit)
-        mfma2 = order == 2 and info["prefix_block"] == BLOCK_MFMA_FP4
+        # order 2 may run on the matrix cores (2 x 2^2 flops per unit), and
+        # orders 5-8 do (variant 8: 2 x 3^k flops per unit)
+        mfma = info["variant"] == 8 or (order == 2 and info["prefix_block"] == BLOCK_MFMA_FP4)
+        flops = 2.0 * 3**order if info["variant"] == 8 else mfma_flops_per_unit(order)
         opu = ops_per_unit(order) if info["variant"] in (1, 2, 5) else ops_per_unit_3k(order)
         out[name] = {"value": work * len(walls) / sum(walls) / 1e12, "kernel_ms": kms,
                      "kernel_value": work / (kms * 1e-3) / 1e12, "variant": info["variant"],
                      "prefix_block": info["prefix_block"],
-                     "ops_per_unit": mfma_flops_per_unit(2) if mfma2 else opu,
-                     "bound": "mfma" if mfma2 else "alu",
-                     "frac": (work * mfma_flops_per_unit(2) / (kms * 1e-3) / 1e12 / MFMA_FP4_PEAK_TFLOPS if mfma2
+                     "ops_per_unit": flops if mfma else opu,
+                     "bound": "mfma" if mfma else "alu",
+                     "frac": (work * flops / (kms * 1e-3) / 1e12 / MFMA_FP4_PEAK_TFLOPS if mfma
                               else work * opu / (kms * 1e-3) / 1e12 / VALU_PEAK_TOPS),
                      "frac_3k_cells": work * ops_per_unit_3k(order) / (kms * 1e-3) / 1e12 / VALU_PEAK_TOPS}
         log(f"{name}: kernel {kms:.3f} ms, {out[name]['kernel_value']:.2f} T, frac {out[name]['frac']:.3f}")

@@ -195,7 +195,8 @@ int epi_scan_timing(epi_ctx *ctx, int32_t scan_id, float ms[4]);
 
 /* Number of combinations C(M, order) of a scan and the kernel variant it ran
  * (0 = per-combination generic kernel, 1 = order-2 reduced-cell kernel,
- * 2 = order-3 reduced-cell kernel) and its prefix block. */
+ * 2 = order-3 reduced-cell kernel, 8 = orders 5-8 on the matrix cores) and its
+ * prefix block. */
 int epi_scan_info(epi_ctx *ctx, int32_t scan_id, uint64_t *n_combinations, int32_t *variant,
                   int32_t *prefix_block);
 
@@ -320,9 +321,14 @@ int epi_batch_destroy(epi_ctx *ctx, int32_t batch_id);
  * choice for the order.  Served requests (epi_server_*) always use the fused
  * kernels. */
 #define EPI_BLOCK_SEGMENTED 64
-/* Orders 4-8: the per-combination kernel that counts all 3^order cells of a
- * combination's table with AND + popcount (Section 2.2 as written).  It is
- * the built-in choice from order 5 on; order 4 uses the reduced-cell kernel
+/* Orders 4-8: all 3^order cells of a combination's table counted.  It is the
+ * built-in choice from order 5 on, as 0/1 matrix products of the cell rows of
+ * the combination's first SNPs (orders 5-6: three, 7-8: four) and of the
+ * others on the matrix cores (variant 8), where n_cases + 2^T n_controls <
+ * 2^24, T = the bit width of the case count (up to 4095 individuals per
+ * class), N <= 16385 and the cell rows of all pairs take at most 1 GiB and fit
+ * the context's budget; else, and at order 4, the per-combination kernel with
+ * AND + popcount (Section 2.2 as written).  Order 4 uses the reduced-cell kernel
  * (the cells with genotypes 0 and 1 counted, the others by
  * inclusion-exclusion from the pair and triplet sub-tables) when its
  * triplet sub-table fits, and this block pins the all-cell kernel instead. */

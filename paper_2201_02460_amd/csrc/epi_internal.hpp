@@ -88,11 +88,80 @@ enum Variant : int32_t {
     kR4 = 5,       // order 4, reduced cells per lane, other cells from the sub-tables
     kSeg = 6,      // any order, segmented: a wave's 64 tables counted to a buffer, then scored
     kF2Fold = 7,   // order 2 scored by the pair sub-table pass of another scan of the same dataset
+    kX = 8,        // orders 5-8, all 3^k cells as matrix products of the cell rows of a combination's
+                   // first and last SNPs
 };
 
 // Kernel instantiation of the segmented variant for order k: generic-order
 // parameter kSegGk + k.
 constexpr int kSegGk = 16;
+// ... and of the all-cell matrix-core kernel (kX): kXGk + k.
+constexpr int kXGk = 32;
+
+// kX: a combination of order k is a subset of its first xa(k) SNPs (A) and one
+// of its last xb(k) (B).  A work unit is xna(k) A subsets by xnb(k) B subsets,
+// whose cell rows fill three 27-row tiles on each side (three pairs, one
+// triple or a third of a quadruple per tile).  The B subsets go in
+// lexicographic order, xnb at a time (a group); a group whose last subset
+// starts at SNP l takes the A subsets of [0, l) in colex order, xna at a time
+// (a unit), up to u units per work item.
+__host__ __device__ constexpr int xa(int k) { return k <= 6 ? 3 : 4; }
+__host__ __device__ constexpr int xb(int k) { return k - xa(k); }
+__host__ __device__ constexpr int x_subsets(int n) { return n == 2 ? 9 : (n == 3 ? 3 : 1); }
+__host__ __device__ constexpr int xna(int k) { return x_subsets(xa(k)); }
+__host__ __device__ constexpr int xnb(int k) { return x_subsets(xb(k)); }
+constexpr int kXUnits = 8;  // most units per work item
+
+// kX packs both classes into one exact float accumulator, 2^sh n(cases) +
+// 2^T n(controls) < 2^24, T = sh + the bit width of the case count: sh = 2
+// where that fits (2047 individuals a class: the cases' field is then a byte
+// offset into the screening table), else 0 (4095 a class).
+__host__ __device__ inline int x_pack_sh(int n_cases, int n_controls) { return q3_pack_fits(n_cases, n_controls) ? 2 : 0; }
+__host__ __device__ inline int x_pack_shift(int n_cases, int sh) {
+    return n_cases <= 0 ? sh : sh + 32 - __builtin_clz((unsigned)n_cases);
+}
+__host__ __device__ inline bool x_pack_fits(int n_cases, int n_controls) {
+    if (n_cases < 0 || n_controls < 0 || n_cases >= (1 << 22) || n_controls >= (1 << 22)) return false;
+    const int T = x_pack_shift(n_cases, 0);
+    return (unsigned long long)n_cases + ((unsigned long long)n_controls << T) < (1ull << 24);
+}
+
+__host__ __device__ inline unsigned long long small_binom(long long n, int k) {
+    if (n < k) return 0;
+    unsigned long long r = 1;
+    for (int i = 0; i < k; ++i) r = r * (unsigned long long)(n - i) / (unsigned)(i + 1);
+    return r;
+}
+
+// First group whose last B subset starts at SNP l or later (l <= M).
+__host__ __device__ inline unsigned long long x_first_group(int k, int M, int l) {
+    const unsigned long long tot = small_binom(M, xb(k)), nb = (unsigned)xnb(k);
+    const unsigned long long before = tot - small_binom(M - l, xb(k));
+    return before >= tot ? (tot + nb - 1) / nb : before / nb;
+}
+__host__ __device__ inline unsigned long long x_units(int k, int l) {
+    return (small_binom(l, xa(k)) + (unsigned)xna(k) - 1) / (unsigned)xna(k);
+}
+// Work items of the groups whose last B subset starts at SNP l.
+__host__ __device__ inline unsigned long long x_items(int k, int M, int u, int l) {
+    return (x_first_group(k, M, l + 1) - x_first_group(k, M, l)) * ((x_units(k, l) + (unsigned)u - 1) / (unsigned)u);
+}
+
+// Cell rows of single SNPs and pairs (kX operands): one 16-byte entry per lane
+// = 96 individuals of one row, a 4-bit float per nibble position and one of
+// three bit planes (bit p of nibble 8 q + t of word q: individual 32 p + 8 q +
+// t of the entry; bit 3 clear).  The x_halves(n_cases) entries of the cases
+// come first, then those of the controls, each class zero-padded; a product
+// step takes two (its lane halves), S3 steps in all.  The M SNPs'
+// [S3][2 halves][3 genotypes and one unused] entries, then the pairs' (colex)
+// [S3][2][9].
+__host__ __device__ constexpr int x_halves(int n) { return (n + 95) / 96; }
+__host__ __device__ constexpr int x_steps(int n0, int n1) { return (x_halves(n0) + x_halves(n1) + 1) / 2; }
+constexpr int kXSingle = 2 * 4 * 16, kXPair = 2 * 9 * 16;  // bytes per step
+__host__ __device__ constexpr unsigned long long x_row_bytes(int M, int S3) {
+    return (unsigned long long)S3 *
+           ((unsigned long long)M * kXSingle + (unsigned long long)M * (M - 1) / 2 * kXPair);
+}
 
 struct DsView {
     const v4u *masks;
@@ -123,10 +192,12 @@ struct Task {
     DsView ds;
     uint32_t *pairs;                  // pair sub-table, 8 u32 per pair (lexicographic, or colex: pair_colex)
     uint32_t *triples;                // colex-ordered triplet sub-table, 8 u32 per triplet (kR4, kF3Emit)
+    const v4u *xrows;                 // kX: cell rows of single SNPs and pairs (layout above)
     uint32_t *seg;                    // kSeg: per wave slot of the launch (4 per workgroup), 2 x 3^k x 64 u32
                                       //   counts, cell-major ([class][cell][lane])
     const unsigned long long *items;  // per-item descriptors: kF3 j<<40 | ib<<20 | mb, kF2 ib<<20 | mb
-                                      // (kF3 with np = kNpMfma: 16-SNP i-block ib, 32-SNP m-block mb)
+                                      // (kF3 with np = kNpMfma: 16-SNP i-block ib, 32-SNP m-block mb);
+                                      // kX: the M + 1 first items of each SNP l, see x_items
     unsigned long long n_items;
     unsigned long long item_base;     // first global item of this task in its launch
     unsigned long long first_item;    // task-local index of the launch's first item of this task
@@ -138,7 +209,7 @@ struct Task {
     unsigned int *hist;               // score histogram, kHistWords counters (null: none)
     unsigned int cand_cap;
     int32_t variant, order, top_k;
-    int32_t np;                       // prefix block (kF2/kF3) or ranks per lane (kGeneric)
+    int32_t np;                       // prefix block (kF2/kF3), ranks per lane (kGeneric), units per item (kX)
     int32_t n_blocks;                 // number of prefix blocks (kF2: i-blocks, kF3: j values + 1)
     int32_t key_bits;                 // bits per index in the packed key
     int32_t cell_shift;               // kF2Emit: pair cells are written as (count << cell_shift)
@@ -179,7 +250,8 @@ struct Task {
 //              SNPs (m = 32 mb ..) from the one holding i0 + 1 on.
 // The host counts a table's items with these functions and the device
 // writes them (items_kernel), group after group.
-enum ItemKind : int32_t { kItemsF2 = 0, kItemsF3 = 1, kItemsF3M = 2, kItemsF3M2 = 3, kItemsF2M = 4 };
+enum ItemKind : int32_t { kItemsF2 = 0, kItemsF3 = 1, kItemsF3M = 2, kItemsF3M2 = 3, kItemsF2M = 4,
+                          kItemsX = 16 /* + order: the first item of each SNP l (np: units per item) */ };
 constexpr int kItemTile = 4;
 constexpr int kStoreChunkBytes = 1024;  // bytes per store_kernel launch
 

@@ -281,6 +281,7 @@ struct TopK {
     int top;         // highest histogram bin this wave has counted (-1: none)
     unsigned long long dsum;  // checking launches: this lane's digest sum and count since the last flush
     unsigned dn;
+    int xl;          // kX: SNP l of the wave's last item (a guess for the next)
     int nohist;      // the item's combinations are already in the histogram (a pilot item)
 };
 
@@ -996,12 +997,12 @@ struct QFmt<false> {
     static EPI_DEV const v4u *qa(const DsView &d) { return d.qa; }
     static EPI_DEV const v4u *qb(const DsView &d) { return d.qb; }
     static EPI_DEV int ks(const DsView &d, int c) { return d.ks[c]; }
-    // sb: exponent scale of the B operand (E8M0, 127 = 2^0)
-    static EPI_DEV acc_t mma(v4u a, v4u b, acc_t c, int sb = 127) {
+    // sb, sa: exponent scales of the operands (E8M0, 127 = 2^0)
+    static EPI_DEV acc_t mma(v4u a, v4u b, acc_t c, int sb = 127, int sa = 127) {
         const v8i a8 = {(int)a[0], (int)a[1], (int)a[2], (int)a[3], 0, 0, 0, 0};
         const v8i b8 = {(int)b[0], (int)b[1], (int)b[2], (int)b[3], 0, 0, 0, 0};
-        // formats 4 / 4: e2m1 for both operands; A scale 127 = 2^0
-        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 4, 4, 0, 127, 0, sb);
+        // formats 4 / 4: e2m1 for both operands
+        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 4, 4, 0, sa, 0, sb);
     }
 };
 
@@ -1460,14 +1461,432 @@ EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *l
 }
 
 // ---------------------------------------------------------------------------
-// kGeneric: any order K.  A work item is 64 * kGenRanks consecutive colex
+// kX: orders 5-8, all 3^K cells on the matrix cores.  The table of a
+// combination is the product of the cell rows of its first xa(K) SNPs (A) and
+// those of its last xb(K) (B): cell (x_A, x_B) = sum over the individuals of
+// row x_A times row x_B, so no sub-table and no inclusion-exclusion.  A unit
+// is 3 x 3 tiles of 32 x 32 products (27 cell rows and 5 spare ones a side):
+// 27 combinations of order 5, 9 of order 6, 3 of order 7, one of order 8.
+//
+// A row is the AND of two entries of the dataset's cell rows (pairs and single
+// SNPs), loaded at 96 individuals per lane entry, three bit planes that one
+// AND with a constant each turns into a step of 4-bit floats: 0.5, 1.0 or 2.0
+// for a set bit, evened out by the product's exponent scale.  The scales also
+// put the sums at 2^-149 per unit, so that an accumulator's bits are the
+// integer itself, and pack the classes into it (x_pack_fits).
+//
+// Per 192 individuals: 27 products (864 matrix-core cycles), mostly 7 or 8
+// loads and 72 vector ANDs.  All cells of a combination are spread over the
+// wave, so its screening sum is one wave reduction and its handling uniform.
+// Bound by the sum of the products and of the scoring's vector and LDS work:
+// two waves a SIMD overlap them only in part (products without the scoring
+// 3.0 ms, scoring without the products 1.5, together 4.3 at order 8, M = 23,
+// N = 2048, against 18.8 ms for the popcount kernel; order 5, M = 60,
+// N = 2000: 2.0 ms against 6.7).
+// ---------------------------------------------------------------------------
+constexpr int pow3c(int k) { return k <= 0 ? 1 : 3 * pow3c(k - 1); }
+
+// Colex unranking without the binomial table (K <= 4, rank < 2^31): index t
+// from the t-th root of t! rank, corrected by its falling factorial.
+template <int K>
+EPI_DEV void colex_unrank_root(unsigned rank, int (&c)[K]) {
+    #pragma unroll
+    for (int t = K; t >= 1; --t) {
+        if (t == 1) {
+            c[0] = (int)rank;
+            break;
+        }
+        const unsigned fact = t == 2 ? 2u : (t == 3 ? 6u : 24u);
+        const unsigned long long want = (unsigned long long)rank * fact;
+        auto fall = [&](int x) {  // x (x - 1) ... (x - t + 1)
+            unsigned long long v = (unsigned long long)x * (unsigned)(x - 1);
+            if (t > 2) v *= (unsigned)(x - 2);
+            if (t > 3) v *= (unsigned)(x - 3);
+            return v;
+        };
+        const float w = (float)want;
+        int x = t == 2 ? (int)sqrtf(w) : (t == 3 ? (int)cbrtf(w) + 1 : (int)sqrtf(sqrtf(w)) + 1);
+        x = max(x, t - 1);
+        while (x > t - 1 && fall(x) > want) --x;
+        while (fall(x + 1) <= want) ++x;
+        c[t - 1] = x;
+        rank = (unsigned)((want - fall(x)) / fact);
+    }
+}
+
+// Inclusive scan over the wave in vector registers (row shifts and broadcasts).
+EPI_DEV unsigned wave_scan_dpp(unsigned v) {
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+EPI_DEV unsigned rl(unsigned v, int lane) { return (unsigned)__builtin_amdgcn_readlane((int)v, lane); }
+
+EPI_DEV long long wave_sum64(long long v) {
+    #pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += (long long)__shfl_xor((unsigned long long)v, off);
+    return (long long)rfl64((unsigned long long)v);
+}
+
+// The operand rows of one side of a unit: a lane's row c < 27 of tile t is the
+// AND of an entry of its own tile (the SNP that runs fastest through the
+// subsets, or the first pair of a quadruple) and one that the tiles mostly
+// share (the rest of the subset); a pair's row is one entry.  An entry is at
+// a lane constant + a scalar + step x stride; rows past the 27th repeat
+// others (their products are left out of every sum).
+template <int S, bool FIRST>  // FIRST: the subset's first SNP runs fastest (colex), else its last
+struct XSide {
+    static constexpr int kOwn = S == 3 ? kXSingle : kXPair;
+    int vo[S == 2 ? 3 : 1], vs;  // lane constants
+    int so[3], ss[3];            // scalars
+    unsigned single0, pair0, S3;
+    EPI_DEV int pair_at(int x, int y) const {
+        return (int)(pair0 + ((unsigned)y * (unsigned)(y - 1) / 2u + (unsigned)x) * S3 * kXPair);
+    }
+    EPI_DEV void init(int c, int h, unsigned steps, int M) {
+        S3 = steps;
+        pair0 = (unsigned)M * S3 * kXSingle;
+        c = c < 27 ? c : c - 9;
+        if constexpr (S == 3 && FIRST) {
+            vo[0] = (h * 4 + c / 9) * 16;
+            vs = (h * 9 + c % 9) * 16;
+        } else if constexpr (S == 3) {
+            vo[0] = (h * 4 + c % 3) * 16;
+            vs = (h * 9 + c / 3) * 16;
+        } else {
+            vo[0] = (h * 9 + (S == 4 ? c / 9 : c % 9)) * 16;
+            vs = (h * 9 + c % 9) * 16;
+        }
+    }
+    // tile t's subset: e wave-uniform (S = 2: the lane's own pair of the tile)
+    EPI_DEV void set(int t, const int (&e)[S]) {
+        if constexpr (S == 2) {
+            if (t > 0) vo[t] = vo[0];
+            so[t] = 0;
+            ss[t] = pair_at(e[0], e[1]);  // added to the lane constant by finish()
+        } else if constexpr (S == 3) {
+            so[t] = (int)((unsigned)(FIRST ? e[0] : e[2]) * S3 * kXSingle);
+            ss[t] = FIRST ? pair_at(e[1], e[2]) : pair_at(e[0], e[1]);
+        } else {
+            so[t] = pair_at(e[0], e[1]) + 3 * t * 16;
+            ss[t] = pair_at(e[2], e[3]);
+        }
+    }
+    EPI_DEV void finish() {
+        if constexpr (S == 2)
+            #pragma unroll
+            for (int t = 0; t < 3; ++t) vo[t] += ss[t];
+    }
+    // whether the three tiles share their second entry
+    EPI_DEV bool same() const { return S != 3 || (ss[1] == ss[0] && ss[2] == ss[0]); }
+    template <int NS>  // second entries to load: none (pairs), 1 (shared) or 3
+    EPI_DEV void load(__amdgpu_buffer_rsrc_t r, int step, v4u (&f1)[3], v4u (&f2)[3]) const {
+        #pragma unroll
+        for (int t = 0; t < NS; ++t) f2[t] = qload(r, vs, ss[t] + step * kXPair);
+        #pragma unroll
+        for (int t = 0; t < 3; ++t) f1[t] = qload(r, vo[S == 2 ? t : 0], so[t] + step * kOwn);
+    }
+};
+
+// A unit's nine tiles over all steps; NA, NB: second entries per side.  The
+// entries of the next step are in flight while one is multiplied: two sets of
+// them where they fit the registers (each plane's operand is one three-input
+// AND of them), else their two-input AND is formed first and the next step's
+// are loaded behind it.
+template <int NA, int NB, class SA, class SB>
+EPI_DEV void x_count(const SA &sa, const SB &sb, __amdgpu_buffer_rsrc_t rx, int H0, int S3, int sh, int T, int h,
+                     v16f (&acc)[3][3]) {
+    #pragma unroll
+    for (int ta = 0; ta < 3; ++ta)
+        #pragma unroll
+        for (int tb = 0; tb < 3; ++tb) acc[ta][tb] = (v16f){};
+    // planes p of a step: products 4^(p - 1), evened out by B's exponent
+    // scale, which also holds the lane half's class
+    auto step = [&](int s, const v4u (&a1)[3], const v4u (&a2)[3], const v4u (&b1)[3], const v4u (&b2)[3], auto two)
+                    __attribute__((always_inline)) {
+        const int ex = 127 - 75 + (2 * s + h < H0 ? sh : T);
+        #pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned plane = 0x11111111u << p;
+            v4u b[3];
+            #pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                if constexpr (two.value && NB > 0) b[x] = b1[x] & b2[NB == 3 ? x : 0] & plane;
+                else b[x] = b1[x] & plane;
+            }
+            #pragma unroll
+            for (int ta = 0; ta < 3; ++ta) {
+                v4u a;
+                if constexpr (two.value && NA > 0) a = a1[ta] & a2[NA == 3 ? ta : 0] & plane;
+                else a = a1[ta] & plane;
+                #pragma unroll
+                for (int tb = 0; tb < 3; ++tb)
+                    acc[ta][tb] = QFmt<false>::mma(a, b[tb], acc[ta][tb], ex + 2 - 2 * p, 127 - 74);
+            }
+        }
+    };
+    v4u a1[3], a2[3], b1[3], b2[3];
+    sa.template load<NA>(rx, 0, a1, a2);
+    sb.template load<NB>(rx, 0, b1, b2);
+    if constexpr (NA + NB <= 2) {
+        v4u c1[3], c2[3], e1[3], e2[3];
+        #pragma unroll 1
+        for (int s = 0; s < S3; s += 2) {
+            const int s1 = min(s + 1, S3 - 1), s2 = min(s + 2, S3 - 1);
+            sa.template load<NA>(rx, s1, c1, c2);
+            sb.template load<NB>(rx, s1, e1, e2);
+            step(s, a1, a2, b1, b2, std::true_type{});
+            __builtin_amdgcn_sched_barrier(0);
+            sa.template load<NA>(rx, s2, a1, a2);
+            sb.template load<NB>(rx, s2, b1, b2);
+            if (s + 1 < S3) step(s + 1, c1, c2, e1, e2, std::true_type{});
+        }
+    } else {
+        #pragma unroll 1
+        for (int s = 0; s < S3; ++s) {
+            v4u ra[3], rb[3];
+            #pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                ra[t] = NA > 0 ? a1[t] & a2[NA == 3 ? t : 0] : a1[t];
+                rb[t] = NB > 0 ? b1[t] & b2[NB == 3 ? t : 0] : b1[t];
+            }
+            const int sn = min(s + 1, S3 - 1);
+            sa.template load<NA>(rx, sn, a1, a2);
+            sb.template load<NB>(rx, sn, b1, b2);
+            step(s, ra, ra, rb, rb, std::false_type{});
+        }
+    }
+}
+
+template <int K, bool CHECK = false, bool PILOT = false>
+EPI_DEV void item_x(const Task &t, unsigned long long local, TopK &tk, Cand *list, long long gthr) {
+    constexpr int KA = xa(K), KB = xb(K), NA = xna(K), NB = xnb(K), READS = 3 * pow3c(K);
+    const DsView d = t.ds;
+    const int M = d.M, lane = lane_id(), h = lane >> 5, c = lane & 31;
+    const int H0 = x_halves(d.ncls[0]), S3 = x_steps(d.ncls[0], d.ncls[1]);
+    const int sh = x_pack_sh(d.ncls[0], d.ncls[1]), T = x_pack_shift(d.ncls[0], sh);
+    const unsigned m0 = (1u << T) - 1u;
+    // item -> (last SNP l below which A lies, group of B subsets, units); the
+    // wave's previous item gives the first guess
+    int lo = 0, hi = M - 1;
+    if (tk.xl < M && t.items[tk.xl] <= local && local < t.items[tk.xl + 1]) lo = hi = tk.xl;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (t.items[mid] <= local) lo = mid; else hi = mid - 1;
+    }
+    const int l = uni(lo);
+    tk.xl = l;
+    const unsigned n_a = (unsigned)small_binom(l, KA), n_b = (unsigned)small_binom(M, KB);
+    const unsigned units = (n_a + NA - 1) / NA, per_group = (units + (unsigned)t.np - 1) / (unsigned)t.np;
+    const unsigned off = (unsigned)(local - t.items[l]);
+    const unsigned grp = uni((int)(off / per_group));
+    const unsigned u0 = uni((int)((off - grp * per_group) * (unsigned)t.np));
+    unsigned n_u = min((unsigned)t.np, units - u0);
+    if (PILOT && KA == 3) n_u = min(n_u, 2u);  // a unit holds several combinations
+    const unsigned rb0 = ((unsigned)x_first_group(K, M, l) + grp) * NB;
+    // lane s < NB: B subset s of the group (lexicographic, the mirror image of
+    // the colex order); lane i < n_u NA: A subset i of the item
+    int eb[KB], ea[KA];
+    {
+        const unsigned r = min(rb0 + (unsigned)min(lane, NB - 1), n_b - 1);
+        int mc[KB];
+        colex_unrank_root<KB>(n_b - 1 - r, mc);
+        #pragma unroll
+        for (int u = 0; u < KB; ++u) eb[u] = M - 1 - mc[KB - 1 - u];
+        colex_unrank_root<KA>(min(u0 * NA + (unsigned)lane, n_a - 1), ea);
+    }
+    const unsigned nb = min((unsigned)NB, n_b - rb0);  // subsets of the group
+    XSide<KB, false> sb_rows;
+    sb_rows.init(c, h, (unsigned)S3, M);
+    #pragma unroll
+    for (int tb = 0; tb < 3; ++tb) {
+        int e[KB];
+        #pragma unroll
+        for (int u = 0; u < KB; ++u)
+            e[u] = KB == 2 ? __shfl(eb[u], 3 * tb + min(c / 9, 2)) : __builtin_amdgcn_readlane(eb[u], KB == 3 ? tb : 0);
+        sb_rows.set(tb, e);
+    }
+    sb_rows.finish();
+    const __amdgpu_buffer_rsrc_t rx =
+        __builtin_amdgcn_make_buffer_rsrc((void *)t.xrows, 0, (int)x_row_bytes(M, S3), kBufWord3);
+    int sb = screen_bound(entry_bound(tk, gthr), t.score_const, d.shift, d.tq, READS);
+    int pilot_best = (int)0x80000000u;
+    constexpr int NB1 = KB == 2 ? 0 : 1;
+    XSide<KA, true> sa_rows;
+    sa_rows.init(c, h, (unsigned)S3, M);
+    // every combination of the item valid: whole groups and units, and all of
+    // A below the group's first B subset
+    const bool all_valid = nb == (unsigned)NB && (u0 + n_u) * NA <= n_a && l <= __builtin_amdgcn_readlane(eb[0], 0);
+    #pragma unroll 1
+    for (unsigned v = 0; v < n_u; ++v) {
+        #pragma unroll
+        for (int ta = 0; ta < 3; ++ta) {
+            const int sub = (int)(v * NA) + (KA == 3 ? ta : 0);
+            int e[KA];
+            #pragma unroll
+            for (int u = 0; u < KA; ++u) e[u] = __builtin_amdgcn_readlane(ea[u], sub);
+            sa_rows.set(ta, e);
+        }
+        v16f acc[3][3];
+        const bool a_same = sa_rows.same(), b_same = sb_rows.same();
+        if (a_same && b_same) {
+            x_count<1, NB1>(sa_rows, sb_rows, rx, H0, S3, sh, T, h, acc);
+        } else {
+            if constexpr (KA == 3 && KB == 3) {
+                if (a_same) x_count<1, 3>(sa_rows, sb_rows, rx, H0, S3, sh, T, h, acc);
+                else x_count<3, 3>(sa_rows, sb_rows, rx, H0, S3, sh, T, h, acc);
+            } else if constexpr (KA == 3) {
+                x_count<3, NB1>(sa_rows, sb_rows, rx, H0, S3, sh, T, h, acc);
+            } else if constexpr (KB == 3) {
+                x_count<1, 3>(sa_rows, sb_rows, rx, H0, S3, sh, T, h, acc);
+            }
+        }
+        // a tile's part of the screening sum, per lane
+        // (eight cells' table reads in flight at a time: with two waves per
+        // SIMD nothing else hides the LDS latency)
+        // rows past a tile's 27 (register 15, and 12 .. 14 of the upper half)
+        // and its columns past 27 count as nothing
+        const unsigned upper = h ? 0u : ~0u;
+        auto cells = [&](const v16f &x, int r) __attribute__((always_inline)) {
+            const unsigned w = __float_as_uint(x[r]);
+            return r < 12 ? w : w & upper;
+        };
+        auto part_as = [&](const v16f &x, auto wide) __attribute__((always_inline)) {
+            unsigned p = 0, q = 0;
+            #pragma unroll
+            for (int r0 = 0; r0 < 15; r0 += 5) {
+                unsigned t0[5], t1[5], ts[5];
+                #pragma unroll
+                for (int r = 0; r < 5; ++r) {
+                    const unsigned w = cells(x, r0 + r);
+                    const unsigned a0 = wide.value ? (w & m0) << 2 : w & m0;
+                    const unsigned a1 = wide.value ? (w >> T) << 2 : (w >> (T - 2)) & ~3u;
+                    t0[r] = ltab(a0);
+                    t1[r] = ltab(a1);
+                    ts[r] = ltab(a0 + a1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                #pragma unroll
+                for (int r = 0; r < 5; ++r) p = add3(p, t0[r], t1[r]);
+                q = add3(q, ts[0], ts[1]);
+                q = add3(q, ts[2], ts[3]);
+                q += ts[4];
+            }
+            return c < 27 ? p - q : 0u;
+        };
+        auto part = [&](const v16f &x) __attribute__((always_inline)) {
+            return sh ? part_as(x, std::false_type{}) : part_as(x, std::true_type{});
+        };
+        const unsigned ra0 = (u0 + v) * NA;  // rank of the unit's first A subset
+        auto valid_at = [&](int a, int b) {   // A subset a of the unit with B subset b of the group
+            return ra0 + (unsigned)a < n_a && (unsigned)b < nb &&
+                   __builtin_amdgcn_readlane(ea[KA - 1], (int)(v * NA) + a) < __builtin_amdgcn_readlane(eb[0], b);
+        };
+        unsigned valid = 0, pass = 0;  // bit a NB + b
+        auto judge = [&](int a, int b, unsigned sum) __attribute__((always_inline)) {
+            const bool ok = all_valid || valid_at(a, b);
+            const int q = a * NB + b;
+            valid |= ok ? 1u << q : 0u;
+            pass |= ok && (int)sum >= sb ? 1u << q : 0u;
+            if constexpr (PILOT)
+                if (ok && lane == q) pilot_best = (int)sum > pilot_best ? (int)sum : pilot_best;
+        };
+        if constexpr (KA == 3) {
+            #pragma unroll
+            for (int ta = 0; ta < 3; ++ta)
+                #pragma unroll
+                for (int tb = 0; tb < 3; ++tb) {
+                    const unsigned sc = wave_scan_dpp(part(acc[ta][tb]));
+                    if constexpr (KB == 2) {
+                        // the nine columns of each of the tile's three pairs, in both halves
+                        const unsigned e0 = rl(sc, 8), e1 = rl(sc, 17), e2 = rl(sc, 31);
+                        const unsigned f0 = rl(sc, 40), f1 = rl(sc, 49), f2 = rl(sc, 63);
+                        judge(ta, 3 * tb, e0 + (f0 - e2));
+                        judge(ta, 3 * tb + 1, (e1 - e0) + (f1 - f0));
+                        judge(ta, 3 * tb + 2, (e2 - e1) + (f2 - f1));
+                    } else {
+                        judge(ta, tb, rl(sc, 63));
+                    }
+                }
+        } else if constexpr (KB == 3) {
+            #pragma unroll
+            for (int tb = 0; tb < 3; ++tb)
+                judge(0, tb, rl(wave_scan_dpp(part(acc[0][tb]) + part(acc[1][tb]) + part(acc[2][tb])), 63));
+        } else {
+            unsigned sum = 0;
+            #pragma unroll
+            for (int ta = 0; ta < 3; ++ta)
+                #pragma unroll
+                for (int tb = 0; tb < 3; ++tb) sum += part(acc[ta][tb]);
+            judge(0, 0, rl(wave_scan_dpp(sum), 63));
+        }
+        if constexpr (PILOT) continue;
+        // combinations that can enter the list: exact score from the same counts
+        unsigned todo = CHECK ? valid : pass;
+        #pragma unroll 1
+        while (todo) {
+            const int q = (int)__builtin_ctz(todo), a = q / NB, b = q - a * NB;
+            todo &= todo - 1;
+            int cc[K];
+            #pragma unroll
+            for (int u = 0; u < KA; ++u) cc[u] = __builtin_amdgcn_readlane(ea[u], (int)(v * NA) + a);
+            #pragma unroll
+            for (int u = 0; u < KB; ++u) cc[KA + u] = __builtin_amdgcn_readlane(eb[u], b);
+            long long num = 0;
+            unsigned long long dsum = 0;
+            #pragma unroll 1
+            for (int tile = 0; tile < 9; ++tile) {
+                const int ta = tile / 3, tb = tile - 3 * ta;
+                if (KA == 3 && ta != a) continue;
+                if (KB == 3 && tb != b) continue;
+                if (KB == 2 && tb != b / 3) continue;
+                v16f x = acc[0][0];
+                #pragma unroll
+                for (int k = 1; k < 9; ++k)
+                    if (tile == k) x = acc[k / 3][k % 3];
+                if (c >= 27 || (KB == 2 && c / 9 != b % 3)) continue;  // the lanes of its columns
+                #pragma unroll
+                for (int r = 0; r < 15; ++r) {
+                    const unsigned w = cells(x, r);
+                    const unsigned n0 = (w & m0) >> sh, n1 = w >> T;
+                    num += cell_term_counted(d.tlog, n0, n1);
+                    if constexpr (CHECK) {
+                        const int row = 8 * (r / 4) + 4 * h + r % 4;
+                        const int xA = KA == 3 ? row : 27 * ta + row;
+                        const int xB = KB == 2 ? c % 9 : (KB == 3 ? c : 27 * tb + c);
+                        const int cell = xA * pow3c(KB) + xB;
+                        dsum += (unsigned long long)n0 * cell_weight(0, cell) +
+                                (unsigned long long)n1 * cell_weight(1, cell);
+                    }
+                }
+            }
+            num = t.score_const + wave_sum64(num);
+            if constexpr (CHECK) {
+                digest_add(tk, lane == 0, combo_hash<K>(cc), (unsigned long long)wave_sum64((long long)dsum));
+                if (!(pass >> q & 1u)) continue;
+            }
+            unsigned long long key = 0;
+            #pragma unroll
+            for (int u = 0; u < K; ++u) key = (key << t.key_bits) | (unsigned long long)cc[u];
+            tk_offer(tk, list, lane == 0, num, key, gthr);
+            sb = screen_bound(entry_bound(tk, gthr), t.score_const, d.shift, d.tq, READS);
+        }
+    }
+    if constexpr (PILOT) pilot_count(tk, t, pilot_best, READS);
+}
+
+// ---------------------------------------------------------------------------
+// kGeneric: any order K (orders 4-8 where kR4 and kX do not fit).  A work item is 64 * kGenRanks consecutive colex
 // ranks; lane l takes ranks l, l + 64, ...  Each lane counts all 3^K cells of
 // its own combination, 27 cells (the last three SNPs) at a time for each
 // genotype choice of the first K - 3 SNPs.
 // ---------------------------------------------------------------------------
 constexpr int kGenRanks = 4;
-
-constexpr int pow3c(int k) { return k <= 0 ? 1 : 3 * pow3c(k - 1); }
 
 template <int K>
 EPI_DEV void colex_unrank(unsigned long long rank, int M, const unsigned long long *binom, int bstride, int (&c)[K]) {
@@ -2069,6 +2488,7 @@ scan_persistent(const Task *__restrict__ tasks, int n_tasks, unsigned long long 
     tk.dsum = 0;
     tk.dn = 0;
     tk.nohist = 0;
+    tk.xl = 0;
     int cur = -1;
     long long gthr = (long long)0x8000000000000000ull;
     const uint32_t *loaded = nullptr;  // dataset whose screening table is in s_tab
@@ -2105,7 +2525,8 @@ scan_persistent(const Task *__restrict__ tasks, int n_tasks, unsigned long long 
             // mirrored half too for the kernels in the signed cell form, when
             // it fits
             const int ent_fwd = T0.ds.N + 1, ent_rev = 2 * T0.ds.N + 2;
-            const bool want = (T0.variant == kF2 || T0.variant == kF2Fold || T0.variant == kF3 || T0.variant == kR4) &&
+            const bool want = (T0.variant == kF2 || T0.variant == kF2Fold || T0.variant == kF3 || T0.variant == kR4 ||
+                               T0.variant == kX) &&
                               ent_fwd <= tab_cap &&
                               (unsigned)(uintptr_t)(lu32 *)s_tab == 0u;
             const bool sgn = T0.variant == kF3 && is_mfma_np(T0.np);
@@ -2210,8 +2631,13 @@ scan_persistent(const Task *__restrict__ tasks, int n_tasks, unsigned long long 
                     else item_f3<NP3, false, CHECK>(T, local, tk, s_list, gthr, s_stage, stage_cap);
                 }
                 break;
+            case kX:
+                // (the host takes it only where the table fits the LDS)
+                if constexpr (GK > kXGk)
+                    if (lds) item_x<GK - kXGk, CHECK>(T, local, tk, s_list, gthr);
+                break;
             case kSeg:
-                if constexpr (GK > kSegGk) {
+                if constexpr (GK > kSegGk && GK < kXGk) {
                     uint32_t *slot = T.seg + (size_t)(blockIdx.x * 4 + wave) * (2 * kWave * pow3c(GK - kSegGk));
                     if (ldt) item_seg<GK - kSegGk, true, CHECK>(T, local, tk, s_list, gthr, binom, bstride, slot);
                     else item_seg<GK - kSegGk, false, CHECK>(T, local, tk, s_list, gthr, binom, bstride, slot);
@@ -2277,6 +2703,10 @@ struct ScanKernelEntry {
         {0, 0, kSegGk + 6, scan_persistent<0, 0, kSegGk + 6, CK>},                                                 \
         {0, 0, kSegGk + 7, scan_persistent<0, 0, kSegGk + 7, CK>},                                                 \
         {0, 0, kSegGk + 8, scan_persistent<0, 0, kSegGk + 8, CK>},                                                 \
+        {0, 0, kXGk + 5, scan_persistent<0, 0, kXGk + 5, CK>}, /* all cells on the matrix cores */               \
+        {0, 0, kXGk + 6, scan_persistent<0, 0, kXGk + 6, CK>},                                                     \
+        {0, 0, kXGk + 7, scan_persistent<0, 0, kXGk + 7, CK>},                                                     \
+        {0, 0, kXGk + 8, scan_persistent<0, 0, kXGk + 8, CK>},                                                     \
         {0, kNpMfma, 0, scan_persistent<0, kNpMfma, 0, CK>}, /* order 3, matrix cores */                         \
         {0, kNpMfmaI8, 0, scan_persistent<0, kNpMfmaI8, 0, CK>},                                                  \
         {0, kNpMfma2, 0, scan_persistent<0, kNpMfma2, 0, CK>},
@@ -2330,6 +2760,7 @@ scan_pilot(const Task *__restrict__ tasks, int n_tasks, unsigned long long total
     tk.dsum = 0;
     tk.dn = 0;
     tk.nohist = 0;
+    tk.xl = 0;
     constexpr bool i8 = NP3 == kNpMfmaI8;
     constexpr int nj = NP3 == kNpMfma2 ? 2 : 1;
     const long long none = (long long)0x8000000000000000ull;
@@ -2362,7 +2793,9 @@ scan_pilot(const Task *__restrict__ tasks, int n_tasks, unsigned long long total
         tk.top = -1;
         tk.added = 0;
         if (ent_fwd <= tab_cap && local < T.n_items) {
-            if constexpr (GK == 4) {
+            if constexpr (GK > kXGk) {
+                item_x<GK - kXGk, false, true>(T, local, tk, s_list, none);
+            } else if constexpr (GK == 4) {
                 item_r4<true, false, true>(T, local, tk, s_list, none, binom, bstride);
             } else if constexpr (NP2 == kNpMfma) {
                 item_f2m<true, false, true>(T, local, tk, s_list, none);
@@ -2931,6 +3364,79 @@ __global__ void qpack_kernel(DsView d, v4u *__restrict__ qa, v4u *__restrict__ q
     qb[(((long long)(s >> 5) * 2 + g) * KS + step) * 64 + 32 * h + (s & 31)] = out | (out << 1);
 }
 
+// Cell rows of the dataset's single SNPs and pairs (layout in
+// epi_internal.hpp): one thread per (SNP or pair; step; half).
+EPI_DEV unsigned spread8(unsigned b) {  // bit t of a byte to bit 4 t
+    b = (b | (b << 12)) & 0x000f000fu;
+    b = (b | (b << 6)) & 0x03030303u;
+    return (b | (b << 3)) & 0x11111111u;
+}
+
+__global__ void __launch_bounds__(256) xrows_kernel(DsView d, v4u *__restrict__ out, unsigned long long total) {
+    const int H0 = x_halves(d.ncls[0]), S3 = x_steps(d.ncls[0], d.ncls[1]);
+    const unsigned long long id = blockIdx.x * 256ull + threadIdx.x;
+    if (id >= total) return;
+    const int h = (int)(id & 1);
+    const unsigned long long rest = id >> 1;
+    const unsigned long long sub = rest / (unsigned)S3;
+    const int s = (int)(rest - sub * (unsigned)S3);
+    v4u *o;
+    int snp[2] = {0, 0}, n = 0;
+    if (sub < (unsigned)d.M) {
+        n = 1;
+        snp[0] = (int)sub;
+        o = out + ((long long)snp[0] * S3 + s) * (kXSingle / 16) + 4 * h;
+    } else {
+        n = 2;
+        const unsigned p = (unsigned)(sub - (unsigned)d.M);
+        int y = (int)((1.0f + sqrtf(1.0f + 8.0f * (float)p)) * 0.5f);
+        while ((unsigned)y * (unsigned)(y - 1) / 2u > p) --y;
+        while ((unsigned)y * (unsigned)(y + 1) / 2u <= p) ++y;
+        snp[1] = y;
+        snp[0] = (int)(p - (unsigned)y * (unsigned)(y - 1) / 2u);
+        o = out + ((long long)d.M * S3 * kXSingle + ((long long)p * S3 + s) * kXPair) / 16 + 9 * h;
+    }
+    const int half = 2 * s + h, cl = half < H0 ? 0 : 1;
+    const int w0 = 3 * (half - (cl ? H0 : 0));  // first 32-individual word in the class
+    const unsigned *m = (const unsigned *)d.masks;
+    unsigned g[2][3][3];  // [SNP][genotype][plane]
+    #pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        const int w = w0 + p, left = d.ncls[cl] - 32 * w;
+        const unsigned vm = left >= 32 ? ~0u : (left <= 0 ? 0u : ((1u << left) - 1u));
+        #pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            unsigned g0 = 0, g1 = 0;
+            if (left > 0) {
+                const long long at = ((long long)(d.wbase[cl] + (w >> 2)) * 2 * d.Mp + snp[u]) * 4 + (w & 3);
+                g0 = m[at];
+                g1 = m[at + 4ll * d.Mp];
+            }
+            g[u][0][p] = g0;
+            g[u][1][p] = g1;
+            g[u][2][p] = vm & ~(g0 | g1);
+        }
+    }
+    auto put = [&](int cell, unsigned p0, unsigned p1, unsigned p2) {
+        v4u e;
+        #pragma unroll
+        for (int q = 0; q < 4; ++q)
+            e[q] = spread8((p0 >> (8 * q)) & 0xffu) | (spread8((p1 >> (8 * q)) & 0xffu) << 1) |
+                   (spread8((p2 >> (8 * q)) & 0xffu) << 2);
+        o[cell] = e;
+    };
+    if (n == 1) {
+        #pragma unroll
+        for (int a = 0; a < 3; ++a) put(a, g[0][a][0], g[0][a][1], g[0][a][2]);
+    } else {
+        #pragma unroll
+        for (int a = 0; a < 3; ++a)
+            #pragma unroll
+            for (int b = 0; b < 3; ++b)
+                put(3 * a + b, g[0][a][0] & g[1][b][0], g[0][a][1] & g[1][b][1], g[0][a][2] & g[1][b][2]);
+    }
+}
+
 // Integer operand copies: one thread per (SNP, genotype, 32-individual step,
 // half); each 16-individual half word becomes 16 bytes, 1 (qa8) or 4 (qb8)
 // per set bit.
@@ -3056,6 +3562,30 @@ __global__ void __launch_bounds__(1024) items_kernel(int kind, int M, int np, un
     }
 }
 
+// kX: first work item of each SNP l = 0 .. M (x_items summed), one workgroup.
+__global__ void __launch_bounds__(1024) xbase_kernel(int order, int M, int u, unsigned long long *__restrict__ out) {
+    __shared__ unsigned long long s_scan[1024];
+    __shared__ unsigned long long s_base;
+    if (threadIdx.x == 0) s_base = 0;
+    __syncthreads();
+    for (int l0 = 0; l0 <= M; l0 += 1024) {
+        const int l = l0 + (int)threadIdx.x;
+        const unsigned long long n = l < M ? x_items(order, M, u, l) : 0ull;
+        s_scan[threadIdx.x] = n;
+        __syncthreads();
+        for (int off = 1; off < 1024; off <<= 1) {
+            const unsigned long long v = (int)threadIdx.x >= off ? s_scan[threadIdx.x - off] : 0ull;
+            __syncthreads();
+            s_scan[threadIdx.x] += v;
+            __syncthreads();
+        }
+        if (l <= M) out[l] = s_base + s_scan[threadIdx.x] - n;
+        __syncthreads();
+        if (threadIdx.x == 1023) s_base += s_scan[1023];
+        __syncthreads();
+    }
+}
+
 // Bytes carried to device memory in a kernel's arguments (the task array of
 // a launch sequence that may not copy from host memory).
 struct StoreChunk {
@@ -3134,6 +3664,10 @@ hipError_t launch_pilot(int np2, int np3, int gk, int grid, hipStream_t st, cons
                         int stage_cap) {
     void (*fn)(const Task *, int, unsigned long long, const unsigned long long *, int, int, int, int) =
         gk == 4               ? scan_pilot<0, 0, 4>
+        : gk == kXGk + 5      ? scan_pilot<0, 0, kXGk + 5>
+        : gk == kXGk + 6      ? scan_pilot<0, 0, kXGk + 6>
+        : gk == kXGk + 7      ? scan_pilot<0, 0, kXGk + 7>
+        : gk == kXGk + 8      ? scan_pilot<0, 0, kXGk + 8>
         : np3 == kNpMfma      ? scan_pilot<0, kNpMfma, 0>
         : np3 == kNpMfmaI8    ? scan_pilot<0, kNpMfmaI8, 0>
         : np3 == kNpMfma2     ? scan_pilot<0, kNpMfma2, 0>
@@ -3183,7 +3717,18 @@ hipError_t launch_init_counters(hipStream_t st, unsigned long long *queues, int 
     return hipGetLastError();
 }
 
+hipError_t launch_xrows(hipStream_t st, const DsView &d, v4u *out) {
+    const int S3 = x_steps(d.ncls[0], d.ncls[1]);
+    const unsigned long long n = ((unsigned)d.M + (unsigned long long)d.M * (d.M - 1) / 2) * S3 * 2;
+    hipLaunchKernelGGL(xrows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d, out, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_items(hipStream_t st, int kind, int M, int np, unsigned long long *out) {
+    if (kind >= kItemsX) {
+        hipLaunchKernelGGL(xbase_kernel, dim3(1), dim3(1024), 0, st, kind - kItemsX, M, np, out);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(items_kernel, dim3(1), dim3(1024), 0, st, kind, M, np, out);
     return hipGetLastError();
 }

@@ -425,6 +425,7 @@ static int tuned_np(Ctx *c, int order, const Dataset *d) {
 // layouts in epi_internal.hpp (item_group); the device writes the tables
 // (items_kernel) and the host only counts their items.
 static int item_kind(int variant, int np) {
+    if (variant > kXGk) return kItemsX + (variant - kXGk);  // (kX tables are cached as variant kXGk + order)
     if (variant != kF3) return np == kNpMfma ? kItemsF2M : kItemsF2;
     if (np == kNpMfma2) return kItemsF3M2;
     return is_mfma_np(np) ? kItemsF3M : kItemsF3;
@@ -432,9 +433,18 @@ static int item_kind(int variant, int np) {
 
 static unsigned long long item_count(int kind, int M, int np) {
     unsigned long long n = 0;
+    if (kind >= kItemsX) {
+        for (int l = 0; l < M; ++l) n += x_items(kind - kItemsX, M, np, l);
+        return n;
+    }
     const long long G = item_groups(kind, M, np);
     for (long long g = 0; g < G; ++g) n += item_group(kind, M, np, g).count;
     return n;
+}
+
+// Bytes of a descriptor table of n items (kX: one entry per SNP and one past).
+static size_t item_bytes(int kind, int M, unsigned long long n) {
+    return (kind >= kItemsX ? (size_t)M + 1 : (size_t)std::max<unsigned long long>(n, 1)) * 8;
 }
 
 // Descriptor table of a shape, built once per context and cached.
@@ -446,7 +456,7 @@ int get_items(Ctx *c, int variant, int M, int np, const void **d, unsigned long 
         const int kind = item_kind(variant, np);
         ItemTable t;
         t.n = item_count(kind, M, np);
-        int rc = c->alloc.alloc(std::max<unsigned long long>(t.n, 1) * 8, &t.d);
+        int rc = c->alloc.alloc(item_bytes(kind, M, t.n), &t.d);
         if (rc) return rc;
         if (t.n) {
             hipError_t e = launch_items(c->stream, kind, M, np, (unsigned long long *)t.d);
@@ -493,7 +503,7 @@ static int plan_items(Ctx *c, Plan *p, int variant, int M, int np, const void **
     const int kind = item_kind(variant, np);
     const unsigned long long cnt = item_count(kind, M, np);
     void *dev = nullptr;
-    if (int rc = plan_alloc(c, p, std::max<unsigned long long>(cnt, 1) * 8, &dev)) return rc;
+    if (int rc = plan_alloc(c, p, item_bytes(kind, M, cnt), &dev)) return rc;
     if (cnt) p->item_gens.push_back(Plan::ItemGen{kind, M, np, dev});
     *d = dev;
     *n = cnt;
@@ -572,6 +582,7 @@ void plan_free(Ctx *c, Plan *p) {
         c->alloc.release(s.pairs);
         c->alloc.release(s.triples);
         c->alloc.release(s.seg);
+        c->alloc.release(s.xrows);
         c->alloc.release(s.cand);
     }
     c->alloc.release(p->d_parts);
@@ -654,7 +665,7 @@ int default_np3(Ctx *c, const Dataset *d) {
 // pairs per wave to save, so there the second counting must be short: M = 298
 // at N = 4000 takes 166 us without and 156 with, at N = 9483 152 and 162.
 int pilot_items_for(int variant, int np, unsigned long long n_items, int top_k, int N, int tab_cap, int waves) {
-    if (!((variant == kF3 && is_mfma_np(np)) || variant == kR4 || variant == kF2) || tab_cap < N + 1) return 0;
+    if (!((variant == kF3 && is_mfma_np(np)) || variant == kR4 || variant == kF2 || variant == kX) || tab_cap < N + 1) return 0;
     if (variant == kF2 && n_items <= (unsigned long long)waves && N > 6000) return 0;
     const unsigned long long want = std::max<unsigned long long>(n_items / 32, 4ull * std::max(top_k, 1));
     const unsigned long long n = std::min({(unsigned long long)waves, n_items, want});
@@ -751,7 +762,7 @@ uint64_t triple_table_bytes(int M) { return binom_u64(M, 3) * 32; }
 int tab_entries_for(const Dataset *d, int variant, int np, bool both) {
     if (variant == kGeneric || variant == kSeg)  // exact int64 table, n = 0 .. N
         return 2 * (d->N + 1) <= Plan::kTabMax ? 2 * (d->N + 1) : 0;
-    if (variant != kF2 && variant != kF3 && variant != kR4) return 0;
+    if (variant != kF2 && variant != kF3 && variant != kR4 && variant != kX) return 0;
     const bool sgn = variant == kF3 && is_mfma_np(np);
     if (both && sgn && 2 * d->N + 2 <= Plan::kTabMax) return 2 * d->N + 2;
     return d->N + 1 <= Plan::kTabMax ? d->N + 1 : 0;
@@ -767,7 +778,8 @@ int tab_entries_for(const Dataset *d, int variant, int np, bool both) {
 // give it (K entries): such scans go to launch groups of their own, so that
 // they do not lower the occupancy of the others.
 bool table_lowers_occupancy(const Dataset *d, int variant, int np, int order, int top_k) {
-    const int np2 = order == 2 ? np : 0, np3 = order == 3 ? np : 0, gk = order >= 4 ? order : 0;
+    const int np2 = order == 2 ? np : 0, np3 = order == 3 ? np : 0,
+              gk = order >= 4 ? (variant == kX ? kXGk : 0) + order : 0;
     const int stage = stage_cap_for(np2, np3, std::max(d->w4[0], d->w4[1]));
     const int ent = tab_entries_for(d, variant, np, false);
     return ent > 0 && wgs_per_cu(np2, np3, gk, ent, top_k, stage) < wgs_per_cu(np2, np3, gk, 0, top_k, stage);
@@ -806,6 +818,31 @@ bool r4_fits(const Dataset *d) {
 // Order 4 runs by reduced cells when they fit, unless the all-cell kernel is
 // pinned for the dataset's size bucket.
 bool use_r4(Ctx *c, const Dataset *d) { return r4_fits(d) && tuned_np_lookup(c, 4, d) != EPI_BLOCK_ALL_CELLS; }
+
+// Orders 5-8 count all cells on the matrix cores (kX) where both classes fit
+// one float accumulator (x_pack_fits: up to 4095 individuals a class), the
+// screening table fits the LDS, and the cell rows of the pairs take at most
+// 1 GiB with 31-bit group and unit numbers; elsewhere the popcount kernel
+// does.  It is faster at every size tried, down to M = 20, N = 1000 at order
+// 5 (a scan takes 203 us against 501) and M = 14, N = 1000 at order 8.
+static constexpr unsigned long long kMaxRowBytes = 1ull << 30;
+static unsigned long long x_bytes(const Dataset *d) {
+    return x_row_bytes(d->M, x_steps(d->n_case, d->n_ctrl));
+}
+static bool x_fits(const Dataset *d, int order) {
+    if (order < 5 || !x_pack_fits(d->n_case, d->n_ctrl) || d->N + 1 > Plan::kTabMax) return false;
+    if (d->M > 4096 || x_bytes(d) > kMaxRowBytes) return false;
+    const unsigned long long lim = 1ull << 31;
+    return binom_u64(d->M, xb(order)) < lim && binom_u64(d->M, xa(order)) < lim &&
+           binom_u64(d->M, order) / (unsigned long long)(xna(order) * xnb(order)) < lim / 2;
+}
+
+// Units per work item: about 16 items per wave of a full launch.
+static int x_units_per_item(Ctx *c, int order, unsigned long long n_combos) {
+    const unsigned long long units = n_combos / (unsigned long long)(xna(order) * xnb(order));
+    return (int)std::max<unsigned long long>(1, std::min<unsigned long long>(kXUnits, units / (c->n_cu * 8ull * 16)));
+}
+
 static bool needs_pairs(const PlanScan &s) {
     return s.variant != kSeg && (s.desc.order == 3 || s.variant == kR4);
 }
@@ -859,6 +896,19 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
             else if (force_np != kForceReducedCells) r4 = r4 && use_r4(c, s.ds);
             s.variant = r4 ? kR4 : kGeneric;
             s.np = kGenRanksHost;
+            if (x_fits(s.ds, o) && (!arena || x_bytes(s.ds) <= arena->cap / 2)) {
+                // without room for its operand rows the scan takes the
+                // per-combination kernel
+                if (plan_alloc(c, p.get(), x_bytes(s.ds), &s.xrows) == EPI_OK) {
+                    s.variant = kX;
+                    s.np = x_units_per_item(c, o, s.n_combos);
+                    if ((rc = plan_items(c, p.get(), kXGk + o, s.ds->M, s.np, &s.items, &s.n_items)))
+                        return cleanup(rc);
+                    continue;
+                }
+                clear_error();
+                s.xrows = nullptr;
+            }
             s.n_items = (s.n_combos + 64ull * kGenRanksHost - 1) / (64ull * kGenRanksHost);
         }
     }
@@ -891,6 +941,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
             if (s.variant == kF2Fold) continue;  // runs in the pair pass
             const bool seg = s.variant == kSeg;
             int key = seg ? 200 + s.desc.order : group_of_order(s.desc.order, s.np);
+            if (s.variant == kX) key = 300 + s.desc.order;
             if (!seg && table_lowers_occupancy(s.ds, s.variant, s.np, s.desc.order, s.desc.top_k)) key += 100;
             LaunchGroup &g = by_key[key];
             g.scans.push_back(i);
@@ -900,6 +951,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
                 g.np2 = g.np3 = 0;
                 g.gk = kSegGk + s.desc.order;
             }
+            if (s.variant == kX) g.gk = kXGk + s.desc.order;
         }
         for (auto &kv : by_key) p->groups.push_back(kv.second);
     } else {
@@ -921,7 +973,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
             } else {
                 g.np2 = 0;
                 g.np3 = 0;
-                g.gk = s.desc.order;
+                g.gk = (s.variant == kX ? kXGk : 0) + s.desc.order;
             }
             g.scans.push_back(i);
             p->groups.push_back(g);
@@ -1036,6 +1088,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
         t.pairs = (uint32_t *)s.pairs;
         t.triples = (uint32_t *)s.triples;
         t.seg = (uint32_t *)s.seg;
+        t.xrows = (const v4u *)s.xrows;
         t.items = (const unsigned long long *)s.items;
         t.n_items = s.n_items;
         t.item_base = 0;
@@ -1172,6 +1225,8 @@ static int plan_enqueue(Ctx *c, Plan *p, hipStream_t st, bool timing, unsigned l
                               hipMemcpyHostToDevice, st));
     }
     HIPCHK(launch_init_counters(st, p->d_queues, p->n_queues, p->d_cand_count, p->d_thr, nt, p->d_hist));
+    for (auto &sc : p->scans)
+        if (sc.variant == kX) HIPCHK(launch_xrows(st, sc.ds->view, (v4u *)sc.xrows));
     int q = 0;
     const bool single = nt == 1 && !p->persistent;
     if (timing && single) HIPCHK(hipEventRecord(p->ev[1], st));
@@ -1364,6 +1419,29 @@ int size_bucket(const Dataset *d) {
 // per-combination item that are below C(M, k).
 static unsigned long long valid_in_items(const PlanScan &s, unsigned long long a, unsigned long long b) {
     const long long M = s.ds->M;
+    if (s.variant == kX) {
+        const int k = s.desc.order, u = s.np, na = xna(k), nb = xnb(k);
+        const unsigned long long tot = binom_u64(M, xb(k));
+        unsigned long long n = 0, base = 0;
+        for (int l = 0; l < M && base < b; ++l) {
+            const unsigned long long items = x_items(k, (int)M, u, l), per = (x_units(k, l) + u - 1) / u;
+            for (unsigned long long i = std::max(a, base); i < std::min(b, base + items); ++i) {
+                const unsigned long long g = (i - base) / per, u0 = (i - base) % per * u;
+                for (int sub = 0; sub < nb; ++sub) {
+                    const unsigned long long r = (x_first_group(k, (int)M, l) + g) * nb + sub;
+                    if (r >= tot) break;
+                    // the subset's first SNP: the A subsets are those below it
+                    int f = l;
+                    while (f > 0 && tot - binom_u64(M - f, xb(k)) > r) --f;
+                    const unsigned long long n_a = binom_u64(f, xa(k));
+                    const unsigned long long lo = std::min(u0 * na, n_a), hi = std::min((u0 + u) * na, n_a);
+                    n += hi - lo;
+                }
+            }
+            base += items;
+        }
+        return n;
+    }
     if (s.variant != kF2 && s.variant != kF3) {
         const unsigned long long per = 64ull * kGenRanksHost;
         const unsigned long long lo = std::min(a * per, s.n_combos), hi = std::min(b * per, s.n_combos);

@@ -76,6 +76,7 @@ struct PlanScan {
     // order 4 by reduced cells: triplet sub-table pass
     void *triples = nullptr;
     int t3_task = -1;
+    void *xrows = nullptr;  // kX: cell rows of the dataset's single SNPs and pairs
     void *seg = nullptr;  // segmented variant: the launch's per-wave table blocks
     unsigned long long t3_items = 0;
     const void *t3_items_d = nullptr;
@@ -221,6 +222,7 @@ hipError_t launch_function(int fn, int order, hipStream_t st, const DsView &d, c
                            const uint32_t *tables, unsigned long long n, void *out, int *err, int grid,
                            long long score_const);
 hipError_t launch_reseed(int n_tasks, hipStream_t st, const Task *tasks, const Cand *results);
+hipError_t launch_xrows(hipStream_t st, const DsView &d, v4u *out);
 hipError_t launch_items(hipStream_t st, int kind, int M, int np, unsigned long long *out);
 hipError_t launch_store(hipStream_t st, const void *src, size_t bytes, void *dst);
 hipError_t launch_scatter(hipStream_t st, const char *block, int top_k, int order, int32_t *combos, float *scores,
