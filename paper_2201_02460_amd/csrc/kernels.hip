@@ -2945,32 +2945,42 @@ __global__ void __launch_bounds__(1024) merge_final_kernel(const Task *__restric
 }
 
 // ---------------------------------------------------------------------------
-// Result tables: one wave per (task, result).  Decodes the combination,
-// converts the score, and counts the full 2 x 3^k table straight from the
-// masks (genotype-2 rows = valid & ~(row0 | row1)).
+// Result tables: a workgroup per (result, task, 256 cells) decodes the
+// combination, converts the score, and counts its part of the full 2 x 3^k
+// table straight from the masks.  It stages the rows of the k SNPs (genotype
+// 2 = valid & ~(row0 | row1)) in LDS, kFinWords 128-individual words at a
+// time; the threads that share a cell (tables of fewer than 256 cells) take
+// every parts-th word of it and add their counts in LDS.  One wave that
+// walked all cells of a result from global memory left the device idle: 2.6
+// ms for the ten 6561-cell tables of an order-8 scan, now 0.03; 81 us for a
+// hundred of order 5, 25 for order 3 at N = 4000.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(64) finalize_kernel(const Task *__restrict__ tasks, const Cand *__restrict__ results,
-                                                      const ResultLayout *__restrict__ layout, char *__restrict__ out) {
+constexpr int kFinThreads = 256, kFinWords = 16;
+
+__global__ void __launch_bounds__(kFinThreads)
+finalize_kernel(const Task *__restrict__ tasks, const Cand *__restrict__ results,
+                const ResultLayout *__restrict__ layout, char *__restrict__ out) {
+    __shared__ v4u s_rows[kMaxBinomOrder * 3][kFinWords];
+    __shared__ unsigned s_cnt[2][kFinThreads];
     const int ti = blockIdx.y;
     const int r = blockIdx.x;
     const Task &t = tasks[ti];
-    const int K = t.top_k;
-    if (r >= K) return;
-    const int k = t.order;
+    const int K = t.top_k, k = t.order, tid = (int)threadIdx.x;
+    int cells = 1;
+    for (int u = 0; u < k; ++u) cells *= 3;
+    const int x0 = (int)blockIdx.z * kFinThreads;
+    if (r >= K || x0 >= cells) return;
     const DsView d = t.ds;
     char *blk = out + layout[ti].offset;
-    int32_t *hdr = (int32_t *)blk;
     int32_t *combos = (int32_t *)(blk + 16);
     float *scores = (float *)(blk + 16 + (long long)K * k * 4);
     uint32_t *tables = (uint32_t *)(blk + 16 + (long long)K * k * 4 + (long long)K * 4);
     const Cand *res = results + (long long)ti * kMaxTopK;
     const unsigned long long sentinel_key = ~0ull;
-    if (r == 0) {
-        int nv = 0;
-        for (int x = threadIdx.x; x < K; x += kWave) nv += res[x].key != sentinel_key ? 1 : 0;
-        #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) nv += __shfl_xor(nv, off);
-        if (threadIdx.x == 0) {
+    if (r == 0 && blockIdx.z == 0) {
+        const int nv = __syncthreads_count(tid < K && res[tid < K ? tid : 0].key != sentinel_key);
+        if (tid == 0) {
+            int32_t *hdr = (int32_t *)blk;
             hdr[0] = nv;
             hdr[1] = *d.err;  // nonzero: the dataset's last packing had invalid input
         }
@@ -2979,74 +2989,57 @@ __global__ void __launch_bounds__(64) finalize_kernel(const Task *__restrict__ t
     if (e.key == sentinel_key) return;
     const int bits = t.key_bits;
     const unsigned long long kmask = (1ull << bits) - 1ull;
-    int c[kMaxBinomOrder];
-    for (int u = 0; u < k; ++u) c[u] = min((int)((e.key >> (bits * (k - 1 - u))) & kmask), d.Mp - 1);
-    if (threadIdx.x < k) combos[r * k + threadIdx.x] = c[threadIdx.x];
-    if (threadIdx.x == 0) scores[r] = (float)(ldexp((double)e.num, -d.shift) / (double)d.N);
-    int cells = 1;
-    for (int u = 0; u < k; ++u) cells *= 3;
+    auto snp = [&](int u) { return min((int)((e.key >> (bits * (k - 1 - u))) & kmask), d.Mp - 1); };
+    if (blockIdx.z == 0) {
+        if (tid < k) combos[r * k + tid] = snp(tid);
+        if (tid == 0) scores[r] = (float)(ldexp((double)e.num, -d.shift) / (double)d.N);
+    }
+    const int here = min(cells - x0, kFinThreads);  // cells of this workgroup
+    const int parts = kFinThreads / here, part = tid / here, xl = tid - part * here;
+    int row[kMaxBinomOrder];  // the cell's row of each SNP
+    #pragma unroll
+    for (int u = kMaxBinomOrder - 1, y = x0 + xl; u >= 0; --u) {
+        row[u] = 3 * u + y % 3;
+        if (u < k) y /= 3;
+    }
+    s_cnt[0][tid] = 0;
+    s_cnt[1][tid] = 0;
     gv4u *gm = (gv4u *)d.masks;
     const long long Mp = d.Mp;
-    if (cells <= 32) {
-        // orders 2-3: lanes that share a cell take every parts-th word of
-        // it, and their counts meet in LDS
-        __shared__ unsigned s_cnt[2][32];
-        const int parts = kWave / cells;
-        s_cnt[threadIdx.x >> 5][threadIdx.x & 31] = 0;
-        __syncthreads();
-        const int x = threadIdx.x % cells, part = threadIdx.x / cells;
-        if (part < parts) {
-            int g[3];
-            for (int u = k - 1, y = x; u >= 0; --u) {
-                g[u] = y % 3;
-                y /= 3;
+    #pragma unroll 1
+    for (int cl = 0; cl < 2; ++cl) {
+        unsigned cnt = 0;
+        #pragma unroll 1
+        for (int w0 = 0; w0 < d.w4[cl]; w0 += kFinWords) {
+            const int n = min(kFinWords, d.w4[cl] - w0);
+            __syncthreads();
+            for (int i = tid; i < k * kFinWords; i += kFinThreads) {
+                const int u = i / kFinWords, w = i % kFinWords;
+                if (w < n) {
+                    const long long off = ((long long)d.wbase[cl] + w0 + w) * 2 * Mp + snp(u);
+                    const v4u r0 = gm[off], r1 = gm[off + Mp];
+                    s_rows[3 * u][w] = r0;
+                    s_rows[3 * u + 1][w] = r1;
+                    s_rows[3 * u + 2][w] = valid_mask(d.ncls[cl], w0 + w) & ~(r0 | r1);
+                }
             }
-            for (int cl = 0; cl < 2; ++cl) {
-                unsigned cnt = 0;
-                #pragma unroll 2
-                for (int w = part; w < d.w4[cl]; w += parts) {
-                    const long long off = ((long long)d.wbase[cl] + w) * 2 * Mp;
-                    const v4u vm = valid_mask(d.ncls[cl], w);
-                    v4u X = vm;
-                    for (int u = 0; u < k; ++u) {
-                        const v4u r0 = gm[off + c[u]];
-                        const v4u r1 = gm[off + Mp + c[u]];
-                        X &= g[u] == 0 ? r0 : (g[u] == 1 ? r1 : (vm & ~(r0 | r1)));
-                    }
+            __syncthreads();
+            if (part < parts)
+                for (int w = part; w < n; w += parts) {
+                    v4u X = s_rows[row[0]][w];
+                    #pragma unroll
+                    for (int u = 1; u < kMaxBinomOrder; ++u)
+                        if (u < k) X &= s_rows[row[u]][w];
                     cnt += __builtin_popcount(X[0]) + __builtin_popcount(X[1]) + __builtin_popcount(X[2]) +
                            __builtin_popcount(X[3]);
                 }
-                atomicAdd(&s_cnt[cl][x], cnt);
-            }
         }
-        __syncthreads();
-        if (threadIdx.x < cells)
-            for (int cl = 0; cl < 2; ++cl) tables[((long long)r * 2 + cl) * cells + threadIdx.x] = s_cnt[cl][threadIdx.x];
-        return;
+        if (part < parts) atomicAdd(&s_cnt[cl][xl], cnt);
     }
-    for (int x = threadIdx.x; x < cells; x += kWave) {
-        int g[kMaxBinomOrder];
-        int y = x;
-        for (int u = k - 1; u >= 0; --u) {
-            g[u] = y % 3;
-            y /= 3;
-        }
-        for (int cl = 0; cl < 2; ++cl) {
-            unsigned cnt = 0;
-            long long off = (long long)d.wbase[cl] * 2 * Mp;
-            for (int w = 0; w < d.w4[cl]; ++w, off += 2 * Mp) {
-                const v4u vm = valid_mask(d.ncls[cl], w);
-                v4u X = vm;
-                for (int u = 0; u < k; ++u) {
-                    const v4u r0 = gm[off + c[u]];
-                    const v4u r1 = gm[off + Mp + c[u]];
-                    X &= g[u] == 0 ? r0 : (g[u] == 1 ? r1 : (vm & ~(r0 | r1)));
-                }
-                cnt += __builtin_popcount(X[0]) + __builtin_popcount(X[1]) + __builtin_popcount(X[2]) +
-                       __builtin_popcount(X[3]);
-            }
-            tables[((long long)r * 2 + cl) * cells + x] = cnt;
-        }
+    __syncthreads();
+    for (int i = tid; i < 2 * here; i += kFinThreads) {
+        const int cl = i / here, x = i - cl * here;
+        tables[((long long)r * 2 + cl) * cells + x0 + x] = s_cnt[cl][x];
     }
 }
 
@@ -3702,9 +3695,10 @@ hipError_t scan_attributes(int np2, int np3, int gk, int *vgprs, int *lds_bytes)
     return hipSuccess;
 }
 
-hipError_t launch_finalize(int n_tasks, int max_k, hipStream_t st, const Task *tasks, const Cand *results,
-                           const ResultLayout *layout, char *out) {
-    hipLaunchKernelGGL(finalize_kernel, dim3(max_k, n_tasks), dim3(kWave), 0, st, tasks, results, layout, out);
+hipError_t launch_finalize(int n_tasks, int max_k, int max_order, hipStream_t st, const Task *tasks,
+                           const Cand *results, const ResultLayout *layout, char *out) {
+    const int z = (pow3i(max_order) + kFinThreads - 1) / kFinThreads;
+    hipLaunchKernelGGL(finalize_kernel, dim3(max_k, n_tasks, z), dim3(kFinThreads), 0, st, tasks, results, layout, out);
     return hipGetLastError();
 }
 

@@ -1254,9 +1254,12 @@ static int plan_enqueue(Ctx *c, Plan *p, hipStream_t st, bool timing, unsigned l
         }
         if (timing && single) HIPCHK(hipEventRecord(p->ev[3], st));
         HIPCHK(launch_merge(nt, st, tasks, (Cand *)p->d_parts, (Cand *)p->d_results));
-        int maxk = 1;
-        for (auto &s : p->scans) maxk = std::max(maxk, s.desc.top_k);
-        HIPCHK(launch_finalize(nt, maxk, st, tasks, (const Cand *)p->d_results, (const ResultLayout *)p->d_layout,
+        int maxk = 1, maxo = 2;
+        for (auto &s : p->scans) {
+            maxk = std::max(maxk, s.desc.top_k);
+            maxo = std::max(maxo, s.desc.order);
+        }
+        HIPCHK(launch_finalize(nt, maxk, maxo, st, tasks, (const Cand *)p->d_results, (const ResultLayout *)p->d_layout,
                                (char *)p->d_out));
     } else {
         // back-to-back: per scan, [pair pass] main merge finalize
@@ -1288,7 +1291,7 @@ static int plan_enqueue(Ctx *c, Plan *p, hipStream_t st, bool timing, unsigned l
             if (timing && single) HIPCHK(hipEventRecord(p->ev[3], st));
             HIPCHK(launch_merge(1, st, tasks + i, (Cand *)p->d_parts + (size_t)i * kMergeParts * kMaxTopK,
                                 (Cand *)p->d_results + (size_t)i * kMaxTopK));
-            HIPCHK(launch_finalize(1, s.desc.top_k, st, tasks + i, (const Cand *)p->d_results + (size_t)i * kMaxTopK,
+            HIPCHK(launch_finalize(1, s.desc.top_k, s.desc.order, st, tasks + i, (const Cand *)p->d_results + (size_t)i * kMaxTopK,
                                    (const ResultLayout *)p->d_layout + i, (char *)p->d_out));
         }
     }

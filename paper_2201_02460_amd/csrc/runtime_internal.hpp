@@ -213,8 +213,8 @@ hipError_t launch_scan(int np2, int np3, int gk, int grid, hipStream_t st, const
 size_t scan_lds_bytes(int tab_cap, int kmax, int stage_cap);
 hipError_t scan_attributes(int np2, int np3, int gk, int *vgprs, int *lds_bytes);
 hipError_t launch_merge(int n_tasks, hipStream_t st, const Task *tasks, Cand *parts, Cand *results);
-hipError_t launch_finalize(int n_tasks, int max_k, hipStream_t st, const Task *tasks, const Cand *results,
-                           const ResultLayout *layout, char *out);
+hipError_t launch_finalize(int n_tasks, int max_k, int max_order, hipStream_t st, const Task *tasks,
+                           const Cand *results, const ResultLayout *layout, char *out);
 hipError_t launch_init_counters(hipStream_t st, unsigned long long *queues, int nq, unsigned *cand_counts,
                                 unsigned long long *thrs, int n_tasks, unsigned *hist);
 // fn 0: genotype rows, 1: contingency tables (of combos), 2: MI (of tables)

@@ -430,16 +430,17 @@ static int run_round(Server *S, RoundDone *done) {
     SRV_HIPCHK(launch_reseed(nt, st, dt, (const Cand *)S->d_results));
     if (!fin.empty()) {
         ResultLayout *hl = (ResultLayout *)S->h_layout[S->buf];
-        int maxk = 1;
+        int maxk = 1, maxo = 2;
         for (size_t i = 0; i < fin.size(); ++i) {
             Request *r = fin[i].first;
             hl[i].offset = (long long)r->slot * S->out_block;
             hl[i].top_k = r->desc.top_k;
             hl[i].order = r->desc.order;
             maxk = std::max(maxk, r->desc.top_k);
+            maxo = std::max(maxo, r->desc.order);
         }
         SRV_HIPCHK(hipMemcpyAsync(S->d_layout, hl, fin.size() * sizeof(ResultLayout), hipMemcpyHostToDevice, st));
-        SRV_HIPCHK(launch_finalize((int)fin.size(), maxk, st, dt, (const Cand *)S->d_results,
+        SRV_HIPCHK(launch_finalize((int)fin.size(), maxk, maxo, st, dt, (const Cand *)S->d_results,
                                    (const ResultLayout *)S->d_layout, (char *)S->d_out));
         for (auto &pr : fin) {
             Request *r = pr.first;
