@@ -11,21 +11,24 @@
 //             stored; genotype 2 is valid & ~(row0 | row1).  Bits past the
 //             class size and SNPs s >= M are zero.  Class 0 = cases.
 //   single  : u32 [Mp][2 classes][2 genotypes] per-SNP class counts of
-//             genotypes 0 and 1.
+//             genotypes 0 and 1, then the same again as 4n - 4 q3_bias(N).
 //   tlog    : i64 [2N + 1], tlog[n] = round(n * ln(n) * 2^shift).
 //   itab    : u32 [2N + 2], t(n) = round(n * ln(n) * 2^tq) mod 2^32 at entries
 //             n = 0 .. N and again at entries 2N + 1 - n (the screening table;
 //             copied to LDS address 0, t(n) is at byte 4n and at byte
 //             q3_bias(N) - 4n).
-//   qa, qb  : the same genotype-0/1 rows as 4-bit floats (e2m1: qa 0x2 = 1.0,
-//             qb 0x6 = 4.0, 0x0 = 0), in the operand order of the 32x32x64 matrix-core
-//             product: one 16-byte entry per lane = 32 individuals of one row.
-//             KS = ks[0] + ks[1] steps of 64 individuals (class 0 first, each
-//             class zero-padded to a multiple of kQStepMultiple steps); half h
-//             of a step holds its
-//             individuals 32h .. 32h+31, two per byte, low nibble first.
-//             qa [((s / 16) * KS + step) * 64 + 32 h + 2 (s % 16) + g]
-//             qb [(((s / 32) * 2 + g) * KS + step) * 64 + 32 h + s % 32]
+//   qa, qb  : the same genotype-0/1 rows as bit planes of 4-bit floats, in the
+//             operand order of the 32x32x64 matrix-core product: one 16-byte
+//             entry per lane = 96 individuals of one row, three planes (bit p
+//             of nibble 8q + t of word q: individual 32p + 8q + t; bit 3
+//             clear), each a step's 4-bit floats after one AND (0.5, 1.0 or
+//             2.0 per set bit).  xs steps of 2 x 96 individuals: the cases'
+//             halves first (xh0 of them), then the controls', zero-padded;
+//             xh0 is a multiple of four (a pair of steps) unless both
+//             classes fit one accumulator (q3_pack_fits), where a step may
+//             hold a half of each.
+//             qa [((s / 16) * xs + step) * 64 + 32 h + 2 (s % 16) + g]
+//             qb [(((s / 32) * 2 + g) * xs + step) * 64 + 32 h + s % 32]
 //   qa8, qb8: the same with 8-bit integer operands (qa8 1, qb8 4) for the
 //             32x32x32 integer product: steps of 32 individuals (ks8 per
 //             class, padded alike), half h = individuals 16h .. 16h+15, one
@@ -59,13 +62,23 @@ constexpr int kNpMfmaI8 = 32;          // the same with 8-bit integer operands
 constexpr int kNpMfma2 = 48;           // 4-bit float operands, two middle SNPs per work item, both
                                        // classes in one accumulator
 
+// Kernel instantiations of block kNpMfma for launch groups whose datasets all
+// have both classes in one accumulator (q3_pack_fits), or all one accumulator
+// per class; kNpMfma itself takes either, dataset by dataset, for groups that
+// mix them (M = 600, N = 8000: 1.40 ms a scan against 1.49 in the mixed kernel,
+// whose second body costs registers; M = 1000, N = 4000: 3.56 and 3.63; a batch
+// of eight scans of both sorts takes 3.5 ms in one launch, 3.8 in two).
+constexpr int kNpMfmaP = 17, kNpMfmaS = 18;
+
 // Prefix blocks of the matrix-core order-3 kernels (their work items and
 // signed cell form differ from the popcount kernels').
-__host__ __device__ constexpr bool is_mfma_np(int np) { return np == kNpMfma || np == kNpMfmaI8 || np == kNpMfma2; }
-constexpr int kQStepMultiple = 4;      // qa / qb: steps per class padded to a multiple of this
+__host__ __device__ constexpr bool is_mfma_np(int np) {
+    return np == kNpMfma || np == kNpMfmaP || np == kNpMfmaS || np == kNpMfmaI8 || np == kNpMfma2;
+}
+constexpr int kQStepMultiple = 4;      // qa8 / qb8: steps per class padded to a multiple of this
 
-// The two-middle-SNP matrix-core kernel scales the control steps' products by
-// 2^(T - 2) (the MFMA's per-block exponent scale), so one float accumulator
+// Matrix-core kernels with one accumulator for both classes scale the control
+// halves' products by 2^(T - 2) (the MFMA's per-block exponent scale), so it
 // holds 4 n(cases) + 2^T n(controls) with T = 2 + bit width of the case
 // count: the cases' field is below 2^T and the sum stays an exact float
 // integer while it is below 2^24.
@@ -77,7 +90,8 @@ __host__ __device__ inline bool q3_pack_fits(int n_cases, int n_controls) {
     return n_cases >= 0 && n_controls >= 0 && T <= 24 &&
            4ull * (unsigned long long)n_cases + ((unsigned long long)n_controls << T) < (1ull << 24);
 }
-constexpr int kQStageSteps = 64;       // matrix-core kernels: steps of j-mask rows staged in LDS
+constexpr int kQStageSteps = 32;       // 4-bit matrix-core kernels: steps of j-mask rows staged in LDS
+constexpr int kQ8StageSteps = 64;      // the 8-bit one
 
 enum Variant : int32_t {
     kGeneric = 0,  // one combination per lane, all 3^k cells counted
@@ -169,14 +183,14 @@ struct DsView {
     const long long *tlog;
     const uint32_t *itab;  // screening table: t(n) = round(n ln n 2^tq) mod 2^32 for
                            // n = 0 .. N, then the same values for n = N .. 0
-    const v4u *qa, *qb;    // 4-bit-float operand copies of the masks
+    const v4u *qa, *qb;    // 4-bit-float operand copies of the masks (bit planes)
     const v4u *qa8, *qb8;  // 8-bit-integer operand copies (null until selected)
     int32_t tq;            // fixed-point scale of itab (2^tq per unit of n ln n)
     int32_t M, Mp, N, shift;
     int32_t ncls[2];
     int32_t w4[2];
     int32_t wbase[2];
-    int32_t ks[2];         // 64-individual steps per class in qa / qb
+    int32_t xh0, xs;       // qa / qb: 96-individual halves of class 0, steps of both classes
     int32_t ks8[2];        // 32-individual steps per class in qa8 / qb8
     const int *err;        // error bits of the dataset's last packing (0: valid input)
 };

@@ -237,22 +237,6 @@ EPI_DEV void mobius4(T (&R)[81]) {
 // the signed cell form.
 constexpr bool odd_twos(int x) { return x == 0 ? false : ((x % 3 == 2) != odd_twos(x / 3)); }
 
-// mobius3 on the signed cell form (B - 4n for odd_twos cells, 4n for the
-// others, each marginal input offset so that the result comes out in that
-// form): a genotype-2 cell is its marginal minus the genotype-0 and -1 cells,
-// which the form turns into one sum of three.
-EPI_DEV void mobius3_signed(unsigned (&R)[27]) {
-    #pragma unroll
-    for (int r = 0; r < 9; ++r) R[18 + r] += R[r] + R[9 + r];
-    #pragma unroll
-    for (int a = 0; a < 3; ++a)
-        #pragma unroll
-        for (int e = 0; e < 3; ++e) R[9 * a + 6 + e] += R[9 * a + e] + R[9 * a + 3 + e];
-    #pragma unroll
-    for (int ab = 0; ab < 9; ++ab) R[3 * ab + 2] += R[3 * ab] + R[3 * ab + 1];
-}
-
-
 // Sub-table passes keep no best-K list.
 EPI_DEV bool is_emit(int variant) { return variant == kF2Emit || variant == kF3Emit; }
 
@@ -957,13 +941,25 @@ EPI_DEV void item_f3(const Task &t, unsigned long long local, TopK &tk, Cand *li
 // (i, j, m) are dot products of 0/1 indicator rows, so the reduced cells of a
 // class are the products (X_i . x_{j,b})^T X_m over its individuals, one
 // matrix-core product per step of individuals, b and d: rows (i, a) are A,
-// the rows of genotype b of SNP j mask A, rows (m, d) are B.  With 4-bit
-// float operands (1.0 = 0x2; v_mfma_scale_f32_32x32x64_f8f6f4, 64
-// individuals per step) products are 0 or 4 and sums stay below 2^24, so the
-// float accumulators hold the exact counts; 8-bit integer operands
-// (v_mfma_i32_32x32x32_i8, 32 per step) give the same integers.  B holds 4
-// for a set bit, so the sums are 4 n: a count is then the byte offset of its
-// entry in the float screening table.  In the 32 x 32 result,
+// the rows of genotype b of SNP j mask A, rows (m, d) are B.  The 4-bit float
+// operands (v_mfma_scale_f32_32x32x64_f8f6f4, 64 individuals a product) are
+// kept as bit planes, 96 individuals per 16-byte entry: one AND (A with its
+// mask, in the same instruction) turns a plane into floats, 0.5, 1.0 or 2.0
+// for a set bit, and B's exponent scale evens that out.  The scales also put
+// the sums at 4 x 2^-149 per count: below 2^24 such a float's bits are the
+// integer 4 n, the byte offset of the count's entry in the screening table.
+// Where both classes fit one accumulator (q3_pack_fits) the lane halves of
+// the controls are scaled further and it holds 4 n(cases) + 2^T n(controls).
+// 8-bit integer operands (v_mfma_i32_32x32x32_i8, 32 a step, B 4 for a set
+// bit) give the same integers.
+//
+// Bound (M = 1000, N = 4000, times of the whole scan less 0.2 ms around it):
+// the counting alone takes 2.1 ms (1.7 without its loads; its products 1.5),
+// the scoring alone 2.0, the LDS time of its 81 table reads a triplet; two
+// waves a SIMD overlap 0.8 of that.  Planes instead of whole 4-bit operands
+// cut the operand loads from nine to three per 192 individuals, which bound
+// the counting before: N = 15001, M = 1001: 15.2 -> 9.2 ms a scan; N = 4000:
+// 4.1 -> 3.6.  Three waves a SIMD (168 registers, spills) took 3.9.  In the 32 x 32 result,
 // lane l holds column l % 32 (SNP m) and rows 8 (r / 4) + 4 (l / 32) + r % 4
 // of its 16 registers r, i.e. both genotypes a of eight SNPs i; the epilogue
 // is that of the popcount kernel.
@@ -974,10 +970,8 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 
 // Descriptor word 3 of a raw (untyped, unswizzled) gfx9 buffer.
 constexpr int kBufWord3 = 0x00020000;
-// Steps of 64 individuals in flight per operand stream.
+// Steps in flight per operand stream of the 8-bit kernel.
 constexpr int kQDepth = kQStepMultiple;
-// Steps whose j-mask rows are staged in LDS at a time (4 entries per step).
-constexpr int kQSeg = kQStageSteps;
 
 EPI_DEV v4u qload(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
     return __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
@@ -996,7 +990,6 @@ struct QFmt<false> {
     typedef v16f acc_t;
     static EPI_DEV const v4u *qa(const DsView &d) { return d.qa; }
     static EPI_DEV const v4u *qb(const DsView &d) { return d.qb; }
-    static EPI_DEV int ks(const DsView &d, int c) { return d.ks[c]; }
     // sb, sa: exponent scales of the operands (E8M0, 127 = 2^0)
     static EPI_DEV acc_t mma(v4u a, v4u b, acc_t c, int sb = 127, int sa = 127) {
         const v8i a8 = {(int)a[0], (int)a[1], (int)a[2], (int)a[3], 0, 0, 0, 0};
@@ -1018,6 +1011,12 @@ struct QFmt<true> {
     }
 };
 
+// Exponent scales of a step's three planes: A 2^-74, B this plus 2 - 2 p for
+// plane p; e: log2 of a count's weight in the accumulator (2: 4 n).
+constexpr int kScaleA = 127 - 74;
+EPI_DEV int plane_scale(int e, int p) { return 127 - 75 + e + 2 - 2 * p; }
+EPI_DEV unsigned plane_bits(int p) { return 0x11111111u << p; }
+
 // ---------------------------------------------------------------------------
 // kF2 with prefix block kNpMfma: order 2 on the matrix cores, the products of
 // the order-3 kernel below without the middle SNP's mask.  A work item is
@@ -1029,10 +1028,11 @@ struct QFmt<true> {
 // Lane l holds column m = 32 mb + l % 32 and both genotypes a of eight SNPs
 // i of each A block (the layout of item_f3m); the epilogue is item_f2's.
 // ---------------------------------------------------------------------------
-template <bool LDS, bool CHECK = false, bool PILOT = false>
+template <bool LDS, bool PK, bool CHECK = false, bool PILOT = false>
 EPI_DEV void item_f2m(const Task &t, unsigned long long local, TopK &tk, Cand *list, long long gthr) {
     static_assert(!PILOT || (LDS && !CHECK), "the pilot pass scores from the LDS table");
     typedef QFmt<false> Q;
+    constexpr int NC = PK ? 1 : 2;  // accumulator sets: both classes in one, or one each
     int pilot_best = (int)0x80000000u;  // PILOT: the lane's best screening sum
     const DsView d = t.ds;
     const unsigned long long dsc = t.items[local];
@@ -1042,62 +1042,67 @@ EPI_DEV void item_f2m(const Task &t, unsigned long long local, TopK &tk, Cand *l
     const int m = mb * 32 + (lane & 31);
     const bool mv = m < d.M;
     const int m_ld = mv ? m : d.M - 1;
-    const int KS = Q::ks(d, 0) + Q::ks(d, 1);
-    const int blk = KS * 1024;  // bytes of one row block
+    const int S3 = d.xs, H0 = d.xh0, T = PK ? q3_pack_shift(d.ncls[0]) : 0;
+    const int blk = S3 * 1024;  // bytes of one row block
     const v4u *qa = Q::qa(d), *qb = Q::qb(d);
     // the second 16-SNP block of i; past the operand copy's last block (its
     // SNPs would be M or more) the first block again, its lanes invalid
     const int nib = (d.M + 15) / 16;
     const int ib1 = 2 * ib + 1 < nib ? 2 * ib + 1 : 2 * ib;
-    __amdgpu_buffer_rsrc_t rA[2];
-    rA[0] = __builtin_amdgcn_make_buffer_rsrc((void *)(qa + (long long)(2 * ib) * KS * 64), 0, blk, kBufWord3);
-    rA[1] = __builtin_amdgcn_make_buffer_rsrc((void *)(qa + (long long)ib1 * KS * 64), 0, blk, kBufWord3);
+    const __amdgpu_buffer_rsrc_t rA0 =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(qa + (long long)(2 * ib) * S3 * 64), 0, blk, kBufWord3);
+    const __amdgpu_buffer_rsrc_t rA1 =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(qa + (long long)ib1 * S3 * 64), 0, blk, kBufWord3);
     const __amdgpu_buffer_rsrc_t rB0 =
-        __builtin_amdgcn_make_buffer_rsrc((void *)(qb + (long long)(2 * mb) * KS * 64), 0, blk, kBufWord3);
+        __builtin_amdgcn_make_buffer_rsrc((void *)(qb + (long long)(2 * mb) * S3 * 64), 0, blk, kBufWord3);
     const __amdgpu_buffer_rsrc_t rB1 =
-        __builtin_amdgcn_make_buffer_rsrc((void *)(qb + (long long)(2 * mb + 1) * KS * 64), 0, blk, kBufWord3);
+        __builtin_amdgcn_make_buffer_rsrc((void *)(qb + (long long)(2 * mb + 1) * S3 * 64), 0, blk, kBufWord3);
     const int vo = lane * 16;
-    typename Q::acc_t acc[2][2][2];  // [class][A block][genotype of m]
+    typename Q::acc_t acc[NC][2][2];  // [class][A block][genotype of m]
     #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < NC; ++c)
         #pragma unroll
         for (int a = 0; a < 2; ++a)
             #pragma unroll
             for (int e = 0; e < 2; ++e) acc[c][a][e] = (typename Q::acc_t){};
-    // the software pipeline of item_f3m: kQDepth steps in flight, both
-    // classes one stream
-    const int ks0 = Q::ks(d, 0);
-    v4u bA0[kQDepth], bA1[kQDepth], bB0[kQDepth], bB1[kQDepth];
-    #pragma unroll
-    for (int u = 0; u < kQDepth; ++u) {
-        const int so = min(u, KS - 1) * 1024;
-        bA0[u] = qload(rA[0], vo, so);
-        bA1[u] = qload(rA[1], vo, so);
-        bB0[u] = qload(rB0, vo, so);
-        bB1[u] = qload(rB1, vo, so);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        const int c0 = c == 0 ? 0 : ks0;
-        const int cn = Q::ks(d, c);
-        #pragma unroll 1
-        for (int k = 0; k < cn; k += kQDepth) {
-            const int g = c0 + k;
-            #pragma unroll
-            for (int u = 0; u < kQDepth; ++u) {
-                acc[c][0][0] = Q::mma(bA0[u], bB0[u], acc[c][0][0]);
-                acc[c][0][1] = Q::mma(bA0[u], bB1[u], acc[c][0][1]);
-                acc[c][1][0] = Q::mma(bA1[u], bB0[u], acc[c][1][0]);
-                acc[c][1][1] = Q::mma(bA1[u], bB1[u], acc[c][1][1]);
-                const int so = min(g + u + kQDepth, KS - 1) * 1024;
-                bA0[u] = qload(rA[0], vo, so);
-                bA1[u] = qload(rA[1], vo, so);
-                bB0[u] = qload(rB0, vo, so);
-                bB1[u] = qload(rB1, vo, so);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+    // the software pipeline of item_f3m
+    struct Ops {
+        v4u a0, a1, b0, b1;
+    };
+    auto load = [&](int s) __attribute__((always_inline)) {
+        const int so = min(s, S3 - 1) * 1024;
+        return Ops{qload(rA0, vo, so), qload(rA1, vo, so), qload(rB0, vo, so), qload(rB1, vo, so)};
+    };
+    auto mul = [&](const Ops &o, int e, auto cls) __attribute__((always_inline)) {
+        constexpr int c = cls.value;
+        #pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const unsigned pb = plane_bits(p);
+            const int sb = plane_scale(e, p);
+            const v4u a0 = o.a0 & pb, a1 = o.a1 & pb, b0 = o.b0 & pb, b1 = o.b1 & pb;
+            acc[c][0][0] = Q::mma(a0, b0, acc[c][0][0], sb, kScaleA);
+            acc[c][0][1] = Q::mma(a0, b1, acc[c][0][1], sb, kScaleA);
+            acc[c][1][0] = Q::mma(a1, b0, acc[c][1][0], sb, kScaleA);
+            acc[c][1][1] = Q::mma(a1, b1, acc[c][1][1], sb, kScaleA);
+            __builtin_amdgcn_sched_barrier(0);
         }
+    };
+    Ops x = load(0);
+    auto run = [&](int from, int to, auto cls) __attribute__((always_inline)) {
+        #pragma unroll 1
+        for (int s = from; s < to; s += 2) {
+            const Ops y = load(s + 1);
+            mul(x, PK && 2 * s + h >= H0 ? T : 2, cls);
+            __builtin_amdgcn_sched_barrier(0);
+            x = load(s + 2);
+            if (s + 1 < to) mul(y, PK && 2 * s + 2 + h >= H0 ? T : 2, cls);
+        }
+    };
+    if constexpr (PK) {
+        run(0, S3, std::integral_constant<int, 0>{});
+    } else {
+        run(0, H0 / 2, std::integral_constant<int, 0>{});  // an even number of steps
+        run(H0 / 2, S3, std::integral_constant<int, NC - 1>{});
     }
     const v4u *single4 = (const v4u *)d.single;
     const v4u sm = single4[m_ld];
@@ -1106,6 +1111,7 @@ EPI_DEV void item_f2m(const Task &t, unsigned long long local, TopK &tk, Cand *l
     // constant)
     auto score_block = [&](const typename Q::acc_t (&c0)[2], const typename Q::acc_t (&c1)[2], int ab)
                            __attribute__((always_inline)) {
+        const unsigned m0 = (1u << T) - 1u;
         const int i_base = ib * 32 + 16 * ab + 2 * h;
         #pragma unroll
         for (int u = 0; u < 8; ++u) {
@@ -1119,7 +1125,10 @@ EPI_DEV void item_f2m(const Task &t, unsigned long long local, TopK &tk, Cand *l
                 #pragma unroll
                 for (int a = 0; a < 2; ++a)
                     #pragma unroll
-                    for (int e = 0; e < 2; ++e) F[c][3 * a + e] = (int)(c == 0 ? c0 : c1)[e][r0 + a] >> kQScaleShift;
+                    for (int e = 0; e < 2; ++e) {
+                        const unsigned w = __float_as_uint((c == 0 ? c0 : c1)[e][r0 + a]);
+                        F[c][3 * a + e] = (int)(PK ? (c == 0 ? (w & m0) >> kQScaleShift : w >> T) : w >> kQScaleShift);
+                    }
                 F[c][2] = si[2 * c + 0];
                 F[c][5] = si[2 * c + 1];
                 F[c][6] = sm[2 * c + 0];
@@ -1152,22 +1161,21 @@ EPI_DEV void item_f2m(const Task &t, unsigned long long local, TopK &tk, Cand *l
             }
         }
     };
-    score_block(acc[0][0], acc[1][0], 0);
-    score_block(acc[0][1], acc[1][1], 1);
+    score_block(acc[0][0], acc[NC - 1][0], 0);
+    score_block(acc[0][1], acc[NC - 1][1], 1);
     if constexpr (PILOT) pilot_count(tk, t, pilot_best, 27);
 }
 
 // PILOT: the histogram-only pass over an item (needs the screening table in
 // LDS): lower bounds of the scores are counted, nothing is offered.
-template <bool LDS, bool REV, bool I8, bool EMIT = false, bool CHECK = false, int NJ = 1, bool PILOT = false>
+// PK: one accumulator per tile for both classes, where q3_pack_fits; always so
+// with two middle SNPs.  (N = 4000: 3.6 ms against 3.7 with one per class,
+// whose steps hold one class each.)
+template <bool LDS, bool REV, bool I8, bool PK, bool EMIT = false, bool CHECK = false, int NJ = 1, bool PILOT = false>
 EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *list, long long gthr, v4u *stage) {
-    static_assert(NJ == 1 || (NJ == 2 && !EMIT && !I8), "two middle SNPs per item: 4-bit scoring kernel only");
+    static_assert(NJ == 1 || (NJ == 2 && PK && !EMIT), "two middle SNPs per item: one accumulator for both classes");
+    static_assert(!(PK && I8), "the 8-bit kernel keeps the classes apart");
     typedef QFmt<I8> Q;
-    // PK (two middle SNPs): one accumulator per tile for both classes, the
-    // control steps' products scaled by 2^(T - 2), so the tile holds
-    // 4 n(cases) + 2^T n(controls) (q3_pack_shift; the host takes this kernel
-    // only where q3_pack_fits)
-    constexpr bool PK = NJ == 2;
     constexpr int NC = PK ? 1 : 2;
     const int T = PK ? q3_pack_shift(t.ds.ncls[0]) : 0;
     const DsView d = t.ds;
@@ -1179,41 +1187,50 @@ EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *l
     const int m = mb * 32 + (lane & 31);
     // The item's middle SNPs jv[0] = j and (NJ = 2) jv[1] = j + 1, which
     // share the i and m blocks and so every operand load of the counting
-    // loop.  jc is a middle SNP below M - 1 for the sub-table reads of lanes
-    // that have no valid triplet (jv[1] may be M - 1).
-    int jv[NJ], jc[NJ], m_ld[NJ];
+    // loop (jv[1] may be M - 1: no valid triplet).
+    int jv[NJ];
     bool mv[NJ];
     #pragma unroll
     for (int jj = 0; jj < NJ; ++jj) {
         jv[jj] = j + jj;
-        jc[jj] = min(jv[jj], d.M - 2);
         mv[jj] = m > jv[jj] && m < d.M;
-        m_ld[jj] = mv[jj] ? m : jc[jj] + 1;
     }
 
-    // sub-table rows the epilogue needs, issued before the counting loop; all
+    // Sub-table rows the epilogue needs, issued before the counting loop; all
     // counts below are 4 n, in the signed form of the epilogue (the pair
-    // sub-table is written that way, singles and class sizes are put in it
-    // here)
-    gv4u *single4 = (gv4u *)d.single;
-    gv4u *pair4 = (gv4u *)t.pairs;
-    const unsigned B = q3_bias(d.N), B4 = 4u * B;
-    const v4u sm = (single4[m_ld[0]] << kQScaleShift) - B4;
+    // sub-table and the second half of `single` are written that way, the
+    // class sizes are put in it here).  They are read through buffer
+    // descriptors, at 32-bit offsets from the block's first row: a lane with
+    // no valid triplet reads another entry, or zeros past the table's end,
+    // and is left out by `valid`.
+    const unsigned B = q3_bias(d.N);
     const unsigned nall[2] = {13u * B - ((unsigned)d.ncls[0] << kQScaleShift),
                               13u * B - ((unsigned)d.ncls[1] << kQScaleShift)};
-    v4u sj[NJ], pjm0[NJ], pjm1[NJ];
-    #pragma unroll
-    for (int jj = 0; jj < NJ; ++jj) {
-        sj[jj] = (((cv4u *)d.single)[jv[jj]] << kQScaleShift) - B4;  // uniform: a scalar load
-        const unsigned long long rjm = pair_row(jc[jj], d.M) + (unsigned)(m_ld[jj] - jc[jj] - 1);
-        pjm0[jj] = pair4[2 * rjm];
-        pjm1[jj] = pair4[2 * rjm + 1];
+    const __amdgpu_buffer_rsrc_t rS =
+        __builtin_amdgcn_make_buffer_rsrc((void *)((const v4u *)d.single + d.Mp), 0, d.Mp * 16, kBufWord3);
+    const unsigned long long pair_bytes = EMIT ? 0ull : pair_row(d.M - 1, d.M) * 32ull;
+    auto pair_rows = [&](int first) {  // rows (first, first + 1) on
+        const unsigned long long at = pair_row(min(first, d.M - 1), d.M) * 32ull, left = pair_bytes - at;
+        return __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)t.pairs + at), 0,
+                                                 (int)(left < 0x7fffffffull ? left : 0x7fffffffull), kBufWord3);
+    };
+    v4u sm, sj[NJ], pjm0[NJ], pjm1[NJ];
+    if constexpr (!EMIT) {
+        sm = qload(rS, m * 16, 0);
+        #pragma unroll
+        for (int jj = 0; jj < NJ; ++jj) {
+            sj[jj] = ((cv4u *)d.single)[d.Mp + jv[jj]];  // uniform: a scalar load
+            const __amdgpu_buffer_rsrc_t rj = pair_rows(jv[jj]);
+            const int vj = (m - jv[jj] - 1) * 32;
+            pjm0[jj] = qload(rj, vj, 0);
+            pjm1[jj] = qload(rj, vj + 16, 0);
+        }
     }
 
     // operands through buffer descriptors (scalar registers): a lane adds
     // its own constant byte offset and a step adds a scalar one, so a step
     // costs no vector address arithmetic
-    const int KS = Q::ks(d, 0) + Q::ks(d, 1);
+    const int KS = I8 ? d.ks8[0] + d.ks8[1] : d.xs;
     const int blk = KS * 1024;  // bytes of one row block
     const v4u *qa = Q::qa(d), *qb = Q::qb(d);
     const __amdgpu_buffer_rsrc_t rA =
@@ -1237,6 +1254,90 @@ EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *l
             for (int b = 0; b < 2; ++b)
                 #pragma unroll
                 for (int e = 0; e < 2; ++e) acc[jj][c][b][e] = (typename Q::acc_t){};
+    // The two mask rows of a middle SNP are the same for every lane of a half
+    // wave: they are staged once per segment of kSeg steps in the wave's LDS
+    // slot (entry jj 4 kSeg + 4 step + 2 h + b) and read back with broadcast
+    // loads.
+    constexpr int kSeg = I8 ? kQ8StageSteps : kQStageSteps;
+    lv4u *slot = (lv4u *)stage;
+    // mask rows of the segment [base, base + kSeg) of the stream
+    auto stage_masks = [&](int base) __attribute__((always_inline)) {
+        const int n = min(kSeg, KS - base);
+        wave_sync();  // the slot's previous rows have been read
+        // all loads issued at once, no branch between them (entries past the
+        // segment repeat its last step's; the slot has room for them)
+        #pragma unroll
+        for (int jj = 0; jj < NJ; ++jj)
+            #pragma unroll
+            for (int e0 = 0; e0 < 4 * kSeg; e0 += kWave) {
+                const int e = min(e0 + lane, 4 * n - 1);
+                const int vje = (((e >> 2) * 64) + 32 * ((e >> 1) & 1) + 2 * (jv[jj] & 15) + (e & 1)) * 16;
+                slot[jj * 4 * kSeg + e0 + lane] = qload(rJ[jj], vje, base * 1024);
+            }
+        wave_sync();
+    };
+    int seg = 0;
+    if constexpr (!I8) {
+        // Both classes' steps form one stream; a step's operands are loaded
+        // while the one before is multiplied (12 products of 32 cycles a
+        // middle SNP against a load from L2, with another wave or two on the
+        // SIMD), in two register sets taken in turn.
+        const int H0 = d.xh0;
+        struct Ops {
+            v4u a, b0, b1;
+        };
+        auto load = [&](int s) __attribute__((always_inline)) {
+            const int so = min(s, KS - 1) * 1024;
+            return Ops{qload(rA, vo, so), qload(rB0, vo, so), qload(rB1, vo, so)};
+        };
+        auto mul = [&](int s, const Ops &o, int e, auto cls) __attribute__((always_inline)) {
+            constexpr int c = cls.value;
+            v4u J[NJ][2];
+            #pragma unroll
+            for (int jj = 0; jj < NJ; ++jj) {
+                const int js = jj * 4 * kSeg + 4 * (s - seg) + 2 * h;
+                J[jj][0] = slot[js];
+                J[jj][1] = slot[js + 1];
+            }
+            #pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const unsigned pb = plane_bits(p);
+                const int sb = plane_scale(e, p);
+                const v4u b0 = o.b0 & pb, b1 = o.b1 & pb;
+                #pragma unroll
+                for (int jj = 0; jj < NJ; ++jj) {
+                    const v4u A0 = o.a & J[jj][0] & pb, A1 = o.a & J[jj][1] & pb;
+                    acc[jj][c][0][0] = Q::mma(A0, b0, acc[jj][c][0][0], sb, kScaleA);
+                    acc[jj][c][0][1] = Q::mma(A0, b1, acc[jj][c][0][1], sb, kScaleA);
+                    acc[jj][c][1][0] = Q::mma(A1, b0, acc[jj][c][1][0], sb, kScaleA);
+                    acc[jj][c][1][1] = Q::mma(A1, b1, acc[jj][c][1][1], sb, kScaleA);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        Ops x = load(0);
+        stage_masks(0);
+        auto run = [&](int from, int to, auto cls) __attribute__((always_inline)) {
+            #pragma unroll 1
+            for (int s = from; s < to; s += 2) {
+                if (s >= seg + kSeg) {
+                    seg += kSeg;
+                    stage_masks(seg);
+                }
+                const Ops y = load(s + 1);
+                mul(s, x, PK && 2 * s + h >= H0 ? T : 2, cls);
+                __builtin_amdgcn_sched_barrier(0);
+                x = load(s + 2);
+                if (s + 1 < to) mul(s + 1, y, PK && 2 * s + 2 + h >= H0 ? T : 2, cls);
+            }
+        };
+        if constexpr (PK) {
+            run(0, KS, std::integral_constant<int, 0>{});
+        } else {
+            run(0, H0 / 2, std::integral_constant<int, 0>{});  // an even number of steps
+            run(H0 / 2, KS, std::integral_constant<int, NC - 1>{});
+        }
+    } else {
     // Software pipeline: the operands of kQDepth steps are in flight while a
     // step is multiplied (a step's products take far less time than a load
     // from L2).  The steps of both classes form one stream, class 0's first
@@ -1246,12 +1347,7 @@ EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *l
     // the loads in step order, each step's refills right after its products:
     // left alone, the scheduler sinks all refills to the end of the unrolled
     // block, and the loop then waits for every load in flight at its top.
-    // The two mask rows of a middle SNP are the same for every lane of a half
-    // wave: they are staged once per segment of kQSeg steps in the wave's LDS
-    // slot (entry jj 4 kQSeg + 4 step + 2 h + b) and read back with broadcast
-    // loads.
-    lv4u *slot = (lv4u *)stage;
-    const int ks0 = Q::ks(d, 0);
+    const int ks0 = d.ks8[0];
     v4u bA[kQDepth], bB0[kQDepth], bB1[kQDepth];
     #pragma unroll
     for (int u = 0; u < kQDepth; ++u) {
@@ -1261,49 +1357,27 @@ EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *l
         bB1[u] = qload(rB1, vo, so);
         __builtin_amdgcn_sched_barrier(0);
     }
-    // mask rows of the segment [base, base + kQSeg) of the stream
-    auto stage_masks = [&](int base) __attribute__((always_inline)) {
-        const int n = min(kQSeg, KS - base);
-        wave_sync();  // the slot's previous rows have been read
-        // all loads issued at once, no branch between them (entries past the
-        // segment repeat its last step's; the slot has room for them)
-        #pragma unroll
-        for (int jj = 0; jj < NJ; ++jj)
-            #pragma unroll
-            for (int e0 = 0; e0 < 4 * kQSeg; e0 += kWave) {
-                const int e = min(e0 + lane, 4 * n - 1);
-                const int vje = (((e >> 2) * 64) + 32 * ((e >> 1) & 1) + 2 * (jv[jj] & 15) + (e & 1)) * 16;
-                slot[jj * 4 * kQSeg + e0 + lane] = qload(rJ[jj], vje, base * 1024);
-            }
-        wave_sync();
-    };
-    int seg = 0;
     stage_masks(0);
     #pragma unroll
     for (int c = 0; c < 2; ++c) {
         const int c0 = c == 0 ? 0 : ks0;
-        const int cn = Q::ks(d, c);
-        const int cc = PK ? 0 : c;                      // accumulator set of the class
-        const int bsc = PK && c == 1 ? 125 + T : 127;   // B scale: 2^(T - 2) for PK's controls
+        const int cn = d.ks8[c];
         #pragma unroll 1
         for (int k = 0; k < cn; k += kQDepth) {
             const int g = c0 + k;  // the group's first step in the stream
-            if (g >= seg + kQSeg) {
-                seg += kQSeg;
+            if (g >= seg + kSeg) {
+                seg += kSeg;
                 stage_masks(seg);
             }
             #pragma unroll
             for (int u = 0; u < kQDepth; ++u) {
-                #pragma unroll
-                for (int jj = 0; jj < NJ; ++jj) {
-                    const int js = jj * 4 * kQSeg + 4 * (g - seg + u) + 2 * h;
-                    const v4u J0 = slot[js], J1 = slot[js + 1];
-                    const v4u A0 = bA[u] & J0, A1 = bA[u] & J1;
-                    acc[jj][cc][0][0] = Q::mma(A0, bB0[u], acc[jj][cc][0][0], bsc);
-                    acc[jj][cc][0][1] = Q::mma(A0, bB1[u], acc[jj][cc][0][1], bsc);
-                    acc[jj][cc][1][0] = Q::mma(A1, bB0[u], acc[jj][cc][1][0], bsc);
-                    acc[jj][cc][1][1] = Q::mma(A1, bB1[u], acc[jj][cc][1][1], bsc);
-                }
+                const int js = 4 * (g - seg + u) + 2 * h;
+                const v4u J0 = slot[js], J1 = slot[js + 1];
+                const v4u A0 = bA[u] & J0, A1 = bA[u] & J1;
+                acc[0][c][0][0] = Q::mma(A0, bB0[u], acc[0][c][0][0]);
+                acc[0][c][0][1] = Q::mma(A0, bB1[u], acc[0][c][0][1]);
+                acc[0][c][1][0] = Q::mma(A1, bB0[u], acc[0][c][1][0]);
+                acc[0][c][1][1] = Q::mma(A1, bB1[u], acc[0][c][1][1]);
                 // refill with the step kQDepth ahead in the stream (the last
                 // steps re-read the stream's last step)
                 const int so = min(g + u + kQDepth, KS - 1) * 1024;
@@ -1314,7 +1388,19 @@ EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *l
             }
         }
     }
+    }
     wave_sync();  // the slot's rows have been read
+
+    // 4 n of a cell in class c (register r of tile (b, e) of middle SNP jj)
+    const unsigned m0 = (1u << T) - 1u;
+    auto count4 = [&](int jj, int c, int b, int e, int r) __attribute__((always_inline)) {
+        if constexpr (I8) {
+            return (unsigned)acc[jj][c][b][e][r];
+        } else {
+            const unsigned w = __float_as_uint(acc[jj][PK ? 0 : c][b][e][r]);
+            return !PK ? w : (c == 0 ? w & m0 : (w >> (T - 2)) & ~3u);
+        }
+    };
 
     if constexpr (EMIT) {
         // triplet sub-table: the 8 cells 4a + 2b + d of the lane's eight
@@ -1331,7 +1417,7 @@ EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *l
                 #pragma unroll
                 for (int a = 0; a < 2; ++a) {
                     auto pk = [&](int b, int e) {
-                        return (unsigned)(int)acc[0][0][b][e][r0 + a] | ((unsigned)(int)acc[0][NC - 1][b][e][r0 + a] << 16);
+                        return count4(0, 0, b, e, r0 + a) | (count4(0, 1, b, e, r0 + a) << 16);
                     };
                     dst[a] = v4u{pk(0, 0), pk(0, 1), pk(1, 0), pk(1, 1)};
                 }
@@ -1340,11 +1426,10 @@ EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *l
         return;
     }
 
-    // Cells F[c][9a + 3b + e] (digit 2: marginal over that SNP, genotype 2
-    // once the inclusion-exclusion has run) in the signed form: a cell with
-    // an odd number of digits 2 is held as B - 4n, the others as 4n (B =
-    // q3_bias(N)).  Each inclusion-exclusion step is then one three-input add
-    // (mobius3_signed), and both forms are byte addresses of the LDS table,
+    // Cells F[c][9a + 3b + e] (digit 2: genotype 2, by inclusion-exclusion) in
+    // the signed form: a cell with an odd number of digits 2 is held as B -
+    // 4n, the others as 4n (B = q3_bias(N)).  Each inclusion-exclusion step is
+    // then one three-input add, and both forms are byte addresses of the LDS table,
     // which holds t(n) at 4n and at B - 4n.  The marginal inputs come in the
     // forms that make the steps come out so: pair cells B - 4n (as the pair
     // pass writes them), single-SNP cells 4n - 4B, the class size 13B - 4n.
@@ -1354,72 +1439,71 @@ EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *l
     int pilot_best = (int)0x80000000u;  // PILOT: the lane's best screening sum
     int sb = 0;
     if constexpr (LDS) sb = screen_bound(entry_bound(tk, gthr), t.score_const, d.shift, d.tq, 81);
+    // Byte offset of pair (i, m) from the block's first row: the entries of
+    // SNP i0 + x start f(x) = x (2 A - x - 1) / 2 - x pairs on, A = M - i0;
+    // for the upper lane half x is 2 more, f(x + 2) - f(x) = 2 A - 2 x - 5.
+    const int i0 = ib * 16, A = d.M - i0;
+    const __amdgpu_buffer_rsrc_t rI = pair_rows(i0);
+    const int h64 = h * 64;
+    auto f32 = [&](int x) { return 32 * (x * (2 * A - x - 1) / 2 - x); };
     #pragma unroll
     for (int jj = 0; jj < NJ; ++jj) {
         const int jm = jv[jj];
-        int i_n = min(i_base, jc[jj] - 1);  // i below the middle SNP for the sub-table reads
-        unsigned long long row_n = pair_row(i_n, d.M);
-        unsigned long long rim = row_n + (unsigned)(m_ld[jj] - i_n - 1);
-        v4u pim_n0 = pair4[2 * rim], pim_n1 = pair4[2 * rim + 1];
+        // the (j, m) table completed (genotype 2 of j, m, both): the marginals
+        // over i, in the form the last inclusion-exclusion step takes
+        // (B - 4n with an even number of digits 2, else 4n - 2B)
+        unsigned P2[2][9];
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const v4u p = c == 0 ? pjm0[jj] : pjm1[jj];
+            P2[c][0] = p[0];
+            P2[c][1] = p[1];
+            P2[c][3] = p[2];
+            P2[c][4] = p[3];
+            P2[c][2] = sj[jj][2 * c] + p[0] + p[1];
+            P2[c][5] = sj[jj][2 * c + 1] + p[2] + p[3];
+            P2[c][6] = sm[2 * c] + p[0] + p[2];
+            P2[c][7] = sm[2 * c + 1] + p[1] + p[3];
+            P2[c][8] = nall[c] + sm[2 * c] + sm[2 * c + 1] + P2[c][2] + P2[c][5];
+        }
+        const int to_j = (jm - m) * 32;  // from pair (i, m) to pair (i, j)
+        int off_n = (m - i0 - 1) * 32 + h * 32 * (2 * A - 5);
+        v4u pim_n0 = qload(rI, off_n, 0), pim_n1 = qload(rI, off_n + 16, 0);
         #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int i = i_base + 4 * (u >> 1) + (u & 1);
-            const int i_ld = i_n;
-            const unsigned long long row_i = row_n;
             const bool valid = mv[jj] && i < jm;
             const v4u pim0 = pim_n0, pim1 = pim_n1;
+            const v4u pij0 = qload(rI, off_n + to_j, 0), pij1 = qload(rI, off_n + to_j + 16, 0);
+            const v4u si = qload(rS, i * 16, 0);
             if (u + 1 < 8) {
                 // next SNP's pair row, in flight while this one is scored
-                i_n = min(i_base + 4 * ((u + 1) >> 1) + ((u + 1) & 1), jc[jj] - 1);
-                row_n = pair_row(i_n, d.M);
-                rim = row_n + (unsigned)(m_ld[jj] - i_n - 1);
-                pim_n0 = pair4[2 * rim];
-                pim_n1 = pair4[2 * rim + 1];
+                const int x = 4 * (u >> 1) + (u & 1), xn = 4 * ((u + 1) >> 1) + ((u + 1) & 1);
+                off_n += (f32(xn) - f32(x)) - (xn - x) * h64;
+                pim_n0 = qload(rI, off_n, 0);
+                pim_n1 = qload(rI, off_n + 16, 0);
             }
-            const v4u si = (single4[i_ld] << kQScaleShift) - B4;
-            const unsigned long long rij = row_i + (unsigned)(jc[jj] - i_ld - 1);
             const int r0 = 4 * (u >> 1) + 2 * (u & 1);
             unsigned F[2][27];
             #pragma unroll
             for (int c = 0; c < 2; ++c) {
-                const v4u pij = pair4[2 * rij + c];
+                const v4u pij = c == 0 ? pij0 : pij1;
                 const v4u pim = c == 0 ? pim0 : pim1;
-                const v4u pjm = c == 0 ? pjm0[jj] : pjm1[jj];
                 #pragma unroll
-                for (int a = 0; a < 2; ++a)
+                for (int a = 0; a < 2; ++a) {
+                    unsigned *G = F[c] + 9 * a;
                     #pragma unroll
-                    for (int b = 0; b < 2; ++b)
+                    for (int b = 0; b < 2; ++b) {
                         #pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            if constexpr (PK) {
-                                // 4 n(cases) + 2^T n(controls): the cases are the low
-                                // T bits, the controls' 4n is the rest shifted down
-                                const unsigned v = (unsigned)acc[jj][0][b][e][r0 + a];
-                                F[c][9 * a + 3 * b + e] = c == 0 ? v & ((1u << T) - 1u) : (v >> (T - 2)) & ~3u;
-                            } else {
-                                F[c][9 * a + 3 * b + e] = (unsigned)(int)acc[jj][c][b][e][r0 + a];
-                            }
-                        }
-                #pragma unroll
-                for (int a = 0; a < 2; ++a)
+                        for (int e = 0; e < 2; ++e) G[3 * b + e] = count4(jj, c, b, e, r0 + a);
+                        G[3 * b + 2] = pij[2 * a + b] + G[3 * b] + G[3 * b + 1];
+                    }
                     #pragma unroll
-                    for (int b = 0; b < 2; ++b) F[c][9 * a + 3 * b + 2] = pij[2 * a + b];
+                    for (int e = 0; e < 2; ++e) G[6 + e] = pim[2 * a + e] + G[e] + G[3 + e];
+                    G[8] = si[2 * c + a] + pij[2 * a] + pij[2 * a + 1] + G[6] + G[7];
+                }
                 #pragma unroll
-                for (int a = 0; a < 2; ++a)
-                    #pragma unroll
-                    for (int e = 0; e < 2; ++e) F[c][9 * a + 6 + e] = pim[2 * a + e];
-                #pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    #pragma unroll
-                    for (int e = 0; e < 2; ++e) F[c][18 + 3 * b + e] = pjm[2 * b + e];
-                F[c][9 * 0 + 8] = si[2 * c + 0];
-                F[c][9 * 1 + 8] = si[2 * c + 1];
-                F[c][18 + 2] = sj[jj][2 * c + 0];
-                F[c][18 + 5] = sj[jj][2 * c + 1];
-                F[c][24] = sm[2 * c + 0];
-                F[c][25] = sm[2 * c + 1];
-                F[c][26] = nall[c];
-                mobius3_signed(F[c]);
+                for (int r = 0; r < 9; ++r) F[c][18 + r] = P2[c][r] + F[c][r] + F[c][9 + r];
             }
             if constexpr (PILOT) {
                 static_assert(LDS && !CHECK && !EMIT, "the pilot pass reads the screening table from LDS");
@@ -2447,7 +2531,7 @@ EPI_DEV void item_r4(const Task &t, unsigned long long local, TopK &tk, Cand *li
 // matrix cores too) set the floor.
 template <int NP2, int NP3, int GK>
 constexpr int scan_waves_per_eu() {
-    return NP3 == kNpMfma2 || NP2 == kNpMfma ? 2
+    return is_mfma_np(NP3) || NP2 == kNpMfma ? 2
                            : (GK >= 4 ? 2 : (GK == 3 ? 3 : (NP3 >= 8 ? 2 : (NP3 >= 4 ? 3 : (NP3 >= 2 ? 4 : (NP2 >= 8 ? 3 : 4))))));
 }
 
@@ -2592,8 +2676,13 @@ scan_persistent(const Task *__restrict__ tasks, int n_tasks, unsigned long long 
             switch (T.variant) {
             case kF2:
                 if constexpr (NP2 == kNpMfma) {
-                    if (lds) item_f2m<true, CHECK>(T, local, tk, s_list, gthr);
-                    else item_f2m<false, CHECK>(T, local, tk, s_list, gthr);
+                    if (q3_pack_fits(T.ds.ncls[0], T.ds.ncls[1])) {
+                        if (lds) item_f2m<true, true, CHECK>(T, local, tk, s_list, gthr);
+                        else item_f2m<false, true, CHECK>(T, local, tk, s_list, gthr);
+                    } else {
+                        if (lds) item_f2m<true, false, CHECK>(T, local, tk, s_list, gthr);
+                        else item_f2m<false, false, CHECK>(T, local, tk, s_list, gthr);
+                    }
                 } else if constexpr (NP2 > 0) {
                     if (lds) item_f2<NP2, false, true, true, CHECK>(T, local, tk, s_list, gthr, s_stage, stage_cap);
                     else item_f2<NP2, false, false, true, CHECK>(T, local, tk, s_list, gthr, s_stage, stage_cap);
@@ -2610,7 +2699,11 @@ scan_persistent(const Task *__restrict__ tasks, int n_tasks, unsigned long long 
                 }
                 break;
             case kF3Emit:
-                if constexpr (NP3 == kNpMfma) item_f3m<false, false, false, true>(T, local, tk, s_list, gthr, s_stage);
+                if constexpr (NP3 == kNpMfma) {
+                    if (q3_pack_fits(T.ds.ncls[0], T.ds.ncls[1]))
+                        item_f3m<false, false, false, true, true>(T, local, tk, s_list, gthr, s_stage);
+                    else item_f3m<false, false, false, false, true>(T, local, tk, s_list, gthr, s_stage);
+                }
                 break;
             case kR4:
                 if constexpr (GK == 4) {
@@ -2622,10 +2715,19 @@ scan_persistent(const Task *__restrict__ tasks, int n_tasks, unsigned long long 
                 if constexpr (is_mfma_np(NP3)) {
                     constexpr bool i8 = NP3 == kNpMfmaI8;
                     constexpr int nj = NP3 == kNpMfma2 ? 2 : 1;
-                    if (lds && loaded_rev)
-                        item_f3m<true, true, i8, false, CHECK, nj>(T, local, tk, s_list, gthr, s_stage);
-                    else if (lds) item_f3m<true, false, i8, false, CHECK, nj>(T, local, tk, s_list, gthr, s_stage);
-                    else item_f3m<false, false, i8, false, CHECK, nj>(T, local, tk, s_list, gthr, s_stage);
+                    auto run = [&](auto pk) __attribute__((always_inline)) {
+                        constexpr bool PK = pk.value;
+                        if (lds && loaded_rev)
+                            item_f3m<true, true, i8, PK, false, CHECK, nj>(T, local, tk, s_list, gthr, s_stage);
+                        else if (lds)
+                            item_f3m<true, false, i8, PK, false, CHECK, nj>(T, local, tk, s_list, gthr, s_stage);
+                        else item_f3m<false, false, i8, PK, false, CHECK, nj>(T, local, tk, s_list, gthr, s_stage);
+                    };
+                    // one accumulator for both classes where they fit
+                    if constexpr (NP3 == kNpMfma2 || NP3 == kNpMfmaP) run(std::true_type{});
+                    else if constexpr (i8 || NP3 == kNpMfmaS) run(std::false_type{});
+                    else if (q3_pack_fits(T.ds.ncls[0], T.ds.ncls[1])) run(std::true_type{});
+                    else run(std::false_type{});
                 } else if constexpr (NP3 > 0) {
                     if (lds) item_f3<NP3, true, CHECK>(T, local, tk, s_list, gthr, s_stage, stage_cap);
                     else item_f3<NP3, false, CHECK>(T, local, tk, s_list, gthr, s_stage, stage_cap);
@@ -2708,6 +2810,8 @@ struct ScanKernelEntry {
         {0, 0, kXGk + 7, scan_persistent<0, 0, kXGk + 7, CK>},                                                     \
         {0, 0, kXGk + 8, scan_persistent<0, 0, kXGk + 8, CK>},                                                     \
         {0, kNpMfma, 0, scan_persistent<0, kNpMfma, 0, CK>}, /* order 3, matrix cores */                         \
+        {0, kNpMfmaP, 0, scan_persistent<0, kNpMfmaP, 0, CK>},                                                    \
+        {0, kNpMfmaS, 0, scan_persistent<0, kNpMfmaS, 0, CK>},                                                    \
         {0, kNpMfmaI8, 0, scan_persistent<0, kNpMfmaI8, 0, CK>},                                                  \
         {0, kNpMfma2, 0, scan_persistent<0, kNpMfma2, 0, CK>},
 
@@ -2798,12 +2902,20 @@ scan_pilot(const Task *__restrict__ tasks, int n_tasks, unsigned long long total
             } else if constexpr (GK == 4) {
                 item_r4<true, false, true>(T, local, tk, s_list, none, binom, bstride);
             } else if constexpr (NP2 == kNpMfma) {
-                item_f2m<true, false, true>(T, local, tk, s_list, none);
+                if (q3_pack_fits(T.ds.ncls[0], T.ds.ncls[1])) item_f2m<true, true, false, true>(T, local, tk, s_list, none);
+                else item_f2m<true, false, false, true>(T, local, tk, s_list, none);
             } else if constexpr (NP2 > 0) {
                 item_f2<NP2, false, true, true, false, true>(T, local, tk, s_list, none, s_stage, stage_cap);
             } else {
-                if (rev) item_f3m<true, true, i8, false, false, nj, true>(T, local, tk, s_list, none, s_stage);
-                else item_f3m<true, false, i8, false, false, nj, true>(T, local, tk, s_list, none, s_stage);
+                auto run = [&](auto pk) __attribute__((always_inline)) {
+                    constexpr bool PK = pk.value;
+                    if (rev) item_f3m<true, true, i8, PK, false, false, nj, true>(T, local, tk, s_list, none, s_stage);
+                    else item_f3m<true, false, i8, PK, false, false, nj, true>(T, local, tk, s_list, none, s_stage);
+                };
+                if constexpr (NP3 == kNpMfma2 || NP3 == kNpMfmaP) run(std::true_type{});
+                else if constexpr (i8 || NP3 == kNpMfmaS) run(std::false_type{});
+                else if (q3_pack_fits(T.ds.ncls[0], T.ds.ncls[1])) run(std::true_type{});
+                else run(std::false_type{});
             }
         }
         // the task's last pilot wave takes the bound
@@ -3318,53 +3430,56 @@ __global__ void singles_kernel(DsView d, uint32_t *__restrict__ single) {
     }
     single[(s * 2 + cl) * 2 + 0] = n0;
     single[(s * 2 + cl) * 2 + 1] = n1;
+    // again in the signed cell form of the matrix-core order-3 kernels
+    const unsigned B4 = 4u * q3_bias(d.N);
+    single[(d.Mp + s) * 4 + cl * 2 + 0] = (n0 << kQScaleShift) - B4;
+    single[(d.Mp + s) * 4 + cl * 2 + 1] = (n1 << kQScaleShift) - B4;
 }
 
 // Matrix-core operand copies of the genotype-0/1 rows: one thread per (SNP,
-// genotype, 64-individual step, half); each 32-individual mask word becomes
-// 32 4-bit floats, low nibble first: 0x2 = 1.0 (qa) or 0x6 = 4.0 (qb) for a
-// set bit.
-__global__ void qpack_kernel(DsView d, v4u *__restrict__ qa, v4u *__restrict__ qb) {
-    const long long KS = d.ks[0] + d.ks[1];
-    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid >= (long long)d.Mp * 2 * KS * 2) return;
-    const int s = (int)(tid % d.Mp);
-    long long rest = tid / d.Mp;
-    const int g = (int)(rest & 1);
-    rest >>= 1;
-    const int h = (int)(rest & 1);
-    const long long step = rest >> 1;
-    const int c = step < d.ks[0] ? 0 : 1;
-    const int widx = 2 * (int)(step - (c == 0 ? 0 : d.ks[0])) + h;  // 32-bit word within the class
-    unsigned word = 0;
-    if ((widx >> 2) < d.w4[c]) {
-        gv4u *gm = (gv4u *)d.masks;
-        word = gm[((long long)(d.wbase[c] + (widx >> 2)) * 2 + g) * d.Mp + s][widx & 3];
-    }
-    // qa: 1.0 = 0x2 per set bit; qb: 4.0 = 0x6 (counts come out as 4 n)
-    v4u out;
-    #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        unsigned x = 0;
-        #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const unsigned b = (word >> (8 * k + 2 * t)) & 3u;
-            x |= (((b & 1u) << 1) | ((b >> 1) << 5)) << (8 * t);
-        }
-        out[k] = x;
-    }
-    qa[((long long)(s >> 4) * KS + step) * 64 + 32 * h + 2 * (s & 15) + g] = out;
-    qb[(((long long)(s >> 5) * 2 + g) * KS + step) * 64 + 32 * h + (s & 31)] = out | (out << 1);
-}
-
-// Cell rows of the dataset's single SNPs and pairs (layout in
-// epi_internal.hpp): one thread per (SNP or pair; step; half).
+// genotype, step, half); an entry is three 32-individual mask words, one per
+// bit plane.
 EPI_DEV unsigned spread8(unsigned b) {  // bit t of a byte to bit 4 t
     b = (b | (b << 12)) & 0x000f000fu;
     b = (b | (b << 6)) & 0x03030303u;
     return (b | (b << 3)) & 0x11111111u;
 }
 
+EPI_DEV v4u planes_entry(unsigned p0, unsigned p1, unsigned p2) {
+    v4u e;
+    #pragma unroll
+    for (int q = 0; q < 4; ++q)
+        e[q] = spread8((p0 >> (8 * q)) & 0xffu) | (spread8((p1 >> (8 * q)) & 0xffu) << 1) |
+               (spread8((p2 >> (8 * q)) & 0xffu) << 2);
+    return e;
+}
+
+__global__ void qpack_kernel(DsView d, v4u *__restrict__ qa, v4u *__restrict__ qb) {
+    const long long S3 = d.xs;
+    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (tid >= (long long)d.Mp * 2 * S3 * 2) return;
+    const int s = (int)(tid % d.Mp);
+    long long rest = tid / d.Mp;
+    const int g = (int)(rest & 1);
+    rest >>= 1;
+    const int h = (int)(rest & 1);
+    const long long step = rest >> 1;
+    const int half = 2 * (int)step + h, c = half < d.xh0 ? 0 : 1;
+    const int w0 = 3 * (half - (c ? d.xh0 : 0));  // the entry's first 32-bit word within the class
+    const unsigned *m = (const unsigned *)d.masks;
+    unsigned word[3];
+    #pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        const int w = w0 + p;
+        word[p] = (w >> 2) < d.w4[c] ? m[(((long long)(d.wbase[c] + (w >> 2)) * 2 + g) * d.Mp + s) * 4 + (w & 3)] : 0u;
+    }
+    const v4u out = planes_entry(word[0], word[1], word[2]);
+    qa[((long long)(s >> 4) * S3 + step) * 64 + 32 * h + 2 * (s & 15) + g] = out;
+    qb[(((long long)(s >> 5) * 2 + g) * S3 + step) * 64 + 32 * h + (s & 31)] = out;
+}
+
+// Cell rows of the dataset's single SNPs and pairs (layout in
+// epi_internal.hpp): one thread per (SNP or pair; step; half).
 __global__ void __launch_bounds__(256) xrows_kernel(DsView d, v4u *__restrict__ out, unsigned long long total) {
     const int H0 = x_halves(d.ncls[0]), S3 = x_steps(d.ncls[0], d.ncls[1]);
     const unsigned long long id = blockIdx.x * 256ull + threadIdx.x;
@@ -3410,14 +3525,7 @@ __global__ void __launch_bounds__(256) xrows_kernel(DsView d, v4u *__restrict__ 
             g[u][2][p] = vm & ~(g0 | g1);
         }
     }
-    auto put = [&](int cell, unsigned p0, unsigned p1, unsigned p2) {
-        v4u e;
-        #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            e[q] = spread8((p0 >> (8 * q)) & 0xffu) | (spread8((p1 >> (8 * q)) & 0xffu) << 1) |
-                   (spread8((p2 >> (8 * q)) & 0xffu) << 2);
-        o[cell] = e;
-    };
+    auto put = [&](int cell, unsigned p0, unsigned p1, unsigned p2) { o[cell] = planes_entry(p0, p1, p2); };
     if (n == 1) {
         #pragma unroll
         for (int a = 0; a < 3; ++a) put(a, g[0][a][0], g[0][a][1], g[0][a][2]);
@@ -3662,6 +3770,8 @@ hipError_t launch_pilot(int np2, int np3, int gk, int grid, hipStream_t st, cons
         : gk == kXGk + 7      ? scan_pilot<0, 0, kXGk + 7>
         : gk == kXGk + 8      ? scan_pilot<0, 0, kXGk + 8>
         : np3 == kNpMfma      ? scan_pilot<0, kNpMfma, 0>
+        : np3 == kNpMfmaP     ? scan_pilot<0, kNpMfmaP, 0>
+        : np3 == kNpMfmaS     ? scan_pilot<0, kNpMfmaS, 0>
         : np3 == kNpMfmaI8    ? scan_pilot<0, kNpMfmaI8, 0>
         : np3 == kNpMfma2     ? scan_pilot<0, kNpMfma2, 0>
         : np2 == kNpMfma      ? scan_pilot<kNpMfma, 0, 0>
@@ -3765,7 +3875,7 @@ hipError_t launch_classidx(hipStream_t st, const uint8_t *pheno, int N, int n_ca
 }
 
 hipError_t launch_qpack(hipStream_t st, const DsView &d, v4u *qa, v4u *qb) {
-    const long long n = (long long)d.Mp * 2 * (d.ks[0] + d.ks[1]) * 2;
+    const long long n = (long long)d.Mp * 2 * d.xs * 2;
     hipLaunchKernelGGL(qpack_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d, qa, qb);
     return hipGetLastError();
 }

@@ -255,9 +255,9 @@ static int ds_layout(Dataset *d, int M, int N, int n_case) {
     d->Mp = (M + 63) / 64 * 64;
     d->w4[0] = (d->n_case + 127) / 128;
     d->w4[1] = (d->n_ctrl + 127) / 128;
-    const int q = 64 * kQStepMultiple;
-    d->ks[0] = (d->n_case + q - 1) / q * kQStepMultiple;
-    d->ks[1] = (d->n_ctrl + q - 1) / q * kQStepMultiple;
+    d->xh0 = x_halves(d->n_case);
+    if (!q3_pack_fits(d->n_case, d->n_ctrl)) d->xh0 = (d->xh0 + 3) / 4 * 4;
+    d->xs = (d->xh0 + x_halves(d->n_ctrl) + 1) / 2;
     const int q8 = 32 * kQStepMultiple;
     d->ks8[0] = (d->n_case + q8 - 1) / q8 * kQStepMultiple;
     d->ks8[1] = (d->n_ctrl + q8 - 1) / q8 * kQStepMultiple;
@@ -285,8 +285,8 @@ static void ds_view(Dataset *d) {
     v.wbase[1] = d->w4[0];
     v.qa = (const v4u *)d->qa;
     v.qb = (const v4u *)d->qb;
-    v.ks[0] = d->ks[0];
-    v.ks[1] = d->ks[1];
+    v.xh0 = d->xh0;
+    v.xs = d->xs;
     v.qa8 = (const v4u *)d->qa8;
     v.qb8 = (const v4u *)d->qb8;
     v.ks8[0] = d->ks8[0];
@@ -298,18 +298,18 @@ static void ds_view(Dataset *d) {
 static size_t qop8_bytes(const Dataset *d) { return (size_t)d->Mp * 2 * (d->ks8[0] + d->ks8[1]) * 32; }
 
 // Bytes of each matrix-core operand copy (qa and qb hold the same rows).
-static size_t qop_bytes(const Dataset *d) { return (size_t)d->Mp * 2 * (d->ks[0] + d->ks[1]) * 32; }
+static size_t qop_bytes(const Dataset *d) { return (size_t)d->Mp * 2 * d->xs * 32; }
 
 static int ds_alloc(Ctx *c, Dataset *d) {
     const size_t mask_bytes = (size_t)(d->w4[0] + d->w4[1]) * 2 * d->Mp * 16;
     int rc;
     if ((rc = c->alloc.alloc(std::max<size_t>(mask_bytes, 16), &d->masks))) return rc;
-    if ((rc = c->alloc.alloc((size_t)d->Mp * 16, &d->single))) return rc;
+    if ((rc = c->alloc.alloc((size_t)d->Mp * 32, &d->single))) return rc;
     if ((rc = c->alloc.alloc(((size_t)2 * d->N + 1) * 8, &d->tlog))) return rc;
     if ((rc = c->alloc.alloc((size_t)d->N * 4, &d->idx))) return rc;
     if ((rc = c->alloc.alloc(((size_t)2 * d->N + 2) * 4, &d->itab))) return rc;
     if ((rc = c->alloc.alloc(256, &d->err))) return rc;
-    d->bytes = mask_bytes + (size_t)d->Mp * 16 + ((size_t)2 * d->N + 1) * 8 + (size_t)d->N * 4;
+    d->bytes = mask_bytes + (size_t)d->Mp * 32 + ((size_t)2 * d->N + 1) * 8 + (size_t)d->N * 4;
     // float accumulation of 0/1 x 4 products is exact while 4 x a class count
     // stays below 2^24
     if (d->N < (1 << 22)) {
@@ -690,6 +690,12 @@ int group_list_cap(int np2, int np3, int gk, int tab_cap, int top_k, int stage_c
 // Whether the dataset can run order-3 block np: the matrix-core blocks need
 // their operand copies, and the two-middle-SNP one its class sizes to fit
 // one float accumulator (q3_pack_fits).
+// The instantiation of a launch group's order-3 block for n datasets, n_pack
+// of them with both classes in one accumulator.
+int np3_group_inst(int np3, int n, int n_pack) {
+    return np3 != kNpMfma ? np3 : (n_pack == n ? kNpMfmaP : (n_pack == 0 ? kNpMfmaS : kNpMfma));
+}
+
 bool np3_usable(const Dataset *d, int np) {
     if (np == kNpMfma) return d->qa != nullptr;
     if (np == kNpMfma2) return d->qa != nullptr && q3_pack_fits(d->n_case, d->n_ctrl);
@@ -731,6 +737,7 @@ int grid_for(Ctx *c, int np2, int np3, int gk, unsigned long long items, int tab
 int stage_cap_for(int np2, int np3, int w4_max) {
     if (np2 == kNpMfma) return 0;  // order 2 on the matrix cores stages nothing
     if (np3 == kNpMfma2) return 8 * kQStageSteps;  // two middle SNPs' mask rows: 4 entries per step each
+    if (np3 == kNpMfmaI8) return 4 * kQ8StageSteps;
     if (is_mfma_np(np3)) return 4 * kQStageSteps;  // j-mask rows: 4 entries per step
     const int rows = std::max(np2 > 0 ? 2 * np2 : 0, np3 > 0 ? 2 * (np3 + 1) : 0);
     if (rows == 0) return 0;
@@ -1007,6 +1014,9 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
     p->n_emit = n_emit;
     p->n_t3 = n_t3;
     for (auto &g : p->groups) {
+        int n_pack = 0;
+        for (int i : g.scans) n_pack += q3_pack_fits(p->scans[i].ds->n_case, p->scans[i].ds->n_ctrl) ? 1 : 0;
+        g.np3 = np3_group_inst(g.np3, (int)g.scans.size(), n_pack);
         unsigned long long tot = 0;
         for (int i : g.scans) tot += p->scans[i].n_items;
         g.total_items = tot;
@@ -2012,7 +2022,8 @@ int epi_set_prefix_block(epi_ctx *ctx, int32_t dataset_id, int32_t order, int32_
         d = it->second.get();
     }
     const bool ok2 = order == 2 && (block == 2 || block == 4 || block == 8 || block == kNpMfma);
-    const bool ok3 = order == 3 && (block == 1 || block == 2 || block == 4 || block == 8 || is_mfma_np(block));
+    const bool ok3 = order == 3 && (block == 1 || block == 2 || block == 4 || block == 8 || block == kNpMfma ||
+                                     block == kNpMfmaI8 || block == kNpMfma2);
     const bool any = order >= EPI_MIN_ORDER && order <= EPI_MAX_ORDER && (block == 0 || block == EPI_BLOCK_SEGMENTED);
     const bool all4 = order >= 4 && order <= EPI_MAX_ORDER && block == EPI_BLOCK_ALL_CELLS;
     if (!ok2 && !ok3 && !any && !all4)

@@ -49,7 +49,7 @@ struct Dataset {
     int M = 0, N = 0, n_case = 0, n_ctrl = 0, Mp = 0, shift = 0;
     int w4[2] = {0, 0};
     void *masks = nullptr, *single = nullptr, *tlog = nullptr, *itab = nullptr, *idx = nullptr, *err = nullptr;
-    int ks[2] = {0, 0};                   // 64-individual steps per class of qa / qb
+    int xh0 = 0, xs = 0;                  // qa / qb: halves of class 0, steps of both classes
     void *qa = nullptr, *qb = nullptr;    // matrix-core operand copies (null: order 3 by popcount only)
     int ks8[2] = {0, 0};                  // 32-individual steps per class of qa8 / qb8
     void *qa8 = nullptr, *qb8 = nullptr;  // integer operand copies, built on first selection
@@ -246,6 +246,7 @@ int tuned_np_lookup(Ctx *c, int order, const Dataset *d);
 bool seg_pinned(Ctx *c, int order, const Dataset *d);
 int default_np3(Ctx *c, const Dataset *d);
 bool np3_usable(const Dataset *d, int np);
+int np3_group_inst(int np3, int n, int n_pack);
 int grid_for(Ctx *c, int np2, int np3, int gk, unsigned long long items, int tab_cap, int kmax, int stage_cap);
 int stage_cap_for(int np2, int np3, int w4_max);
 int tab_entries_for(const Dataset *d, int variant, int np, bool both);

@@ -347,6 +347,12 @@ static int run_round(Server *S, RoundDone *done) {
         }
         if (orders.empty()) continue;
         pick_group_kernel(orders, np_hint, &g.np2, &g.np3, &g.gk);
+        int n_pack = 0;
+        for (int i = 0; i < nt; ++i) {
+            const Request *r = order[i].first;
+            if (round_group(r) == key) n_pack += q3_pack_fits(r->ds->n_case, r->ds->n_ctrl) ? 1 : 0;
+        }
+        g.np3 = np3_group_inst(g.np3, (int)orders.size(), n_pack);
         g.stage = stage_cap_for(g.np2, g.np3, 0);
         int cap_both = 0, cap_first = 0;
         std::vector<Request *> members;  // the group's requests, in copy order
@@ -645,7 +651,8 @@ int epi_server_start(epi_ctx *ctx, const epi_server_config *cfg, int32_t *server
     S->budget = cfg->request_budget ? cfg->request_budget : C->alloc.budget;
     // the largest persistent grid any round may launch (in 4-wave workgroups)
     static const int kRoundKernels[][3] = {{2, 0, 0}, {4, 0, 0}, {8, 0, 0}, {0, 1, 0}, {0, 2, 0}, {0, 4, 0},
-                                           {0, 8, 0}, {0, kNpMfma, 0}, {0, kNpMfma2, 0}, {0, kNpMfmaI8, 0},
+                                           {0, 8, 0}, {0, kNpMfma, 0}, {0, kNpMfmaP, 0}, {0, kNpMfmaS, 0},
+                                           {0, kNpMfma2, 0}, {0, kNpMfmaI8, 0},
                                            {0, 0, 4}, {0, 0, 5}, {kNpMfma, 0, 0}};
     S->grid_max = 1;
     for (const auto &k : kRoundKernels)
