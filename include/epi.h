@@ -351,8 +351,8 @@ int epi_batch_destroy(epi_ctx *ctx, int32_t batch_id);
  * items hold different numbers of combinations compare fairly.  The choice
  * is also written to the cache file named by EPI_TUNE_CACHE (if set).  Scans
  * (plain, batched and served) use tuned choices automatically; untuned
- * shapes use built-in defaults (order 3: the matrix-core kernel where
- * available).  *choice receives the chosen block. */
+ * shapes use built-in defaults (order 2: the matrix cores from 1000 SNPs on,
+ * else prefix block 4; order 3: the matrix-core kernel where available).  *choice receives the chosen block. */
 int epi_autotune(epi_ctx *ctx, int32_t dataset_id, int32_t order, int32_t *choice);
 
 /* The candidates of the last epi_autotune of `order` for the dataset's size

@@ -414,11 +414,19 @@ bool seg_pinned(Ctx *c, int order, const Dataset *d) {
     return c->seg_pins.count(TuneKey{order, bucket}) != 0;
 }
 
+// Prefix block of an order-2 scan: the tuned value, else the matrix cores
+// from M = 1000 on and popcount block 4 below.  (us a scan, block 4 / matrix
+// cores: M = 600, N = 500 102 / 133, N = 2000 114 / 139; M = 1000, N = 1000
+// 132 / 112, N = 4000 168 / 125; M = 4000, N = 500 516 / 244, N = 4000 655 /
+// 280: below, the 32 x 32 blocks are too few to fill the device.)
+int default_np2(Ctx *c, const Dataset *d) {
+    const int t = tuned_np_lookup(c, 2, d);
+    if (t > 0 && (t != kNpMfma || d->qa)) return t;
+    return d->qa && d->M >= 1000 ? kNpMfma : 4;
+}
+
 static int tuned_np(Ctx *c, int order, const Dataset *d) {
-    if (order == 3) return default_np3(c, d);
-    const int t = tuned_np_lookup(c, order, d);
-    if (t > 0 && (order != 2 || t != kNpMfma || d->qa)) return t;
-    return order == 2 ? 4 : kGenRanksHost;
+    return order == 2 ? default_np2(c, d) : default_np3(c, d);
 }
 
 // Work items of the order-2 and order-3 kernels: kinds, groups and item
@@ -661,12 +669,13 @@ int default_np3(Ctx *c, const Dataset *d) {
 // without, 178 with; M = 200, N = 2000, K = 100: 1503 and 273).  Its items
 // are counted twice, so it takes 1/32 of the scan (1/16 cost M = 461,
 // N = 7086 0.5 %), or 4 K items where that is more, and at most one item per
-// wave, which large scans reach.  An order-2 scan whose items all run at once has only a few hundred
-// pairs per wave to save, so there the second counting must be short: M = 298
-// at N = 4000 takes 166 us without and 156 with, at N = 9483 152 and 162.
+// wave, which large scans reach.  An order-2 scan of few items has little to
+// save, so there the second counting must be short: M = 298 (about 210 items)
+// at N = 4000 takes 166 us without and 156 with, at N = 9483 152 and 162, but
+// M = 600 (780 items) at N = 8000 401 and 171.
 int pilot_items_for(int variant, int np, unsigned long long n_items, int top_k, int N, int tab_cap, int waves) {
     if (!((variant == kF3 && is_mfma_np(np)) || variant == kR4 || variant == kF2 || variant == kX) || tab_cap < N + 1) return 0;
-    if (variant == kF2 && n_items <= (unsigned long long)waves && N > 6000) return 0;
+    if (variant == kF2 && n_items <= 256 && N > 6000) return 0;
     const unsigned long long want = std::max<unsigned long long>(n_items / 32, 4ull * std::max(top_k, 1));
     const unsigned long long n = std::min({(unsigned long long)waves, n_items, want});
     return (int)((n + 3) & ~3ull);

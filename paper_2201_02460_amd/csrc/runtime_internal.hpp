@@ -244,6 +244,7 @@ int size_bucket(const Dataset *d);
 bool r4_fits(const Dataset *d);
 int tuned_np_lookup(Ctx *c, int order, const Dataset *d);
 bool seg_pinned(Ctx *c, int order, const Dataset *d);
+int default_np2(Ctx *c, const Dataset *d);
 int default_np3(Ctx *c, const Dataset *d);
 bool np3_usable(const Dataset *d, int np);
 int np3_group_inst(int np3, int n, int n_pack);

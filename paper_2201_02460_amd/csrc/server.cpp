@@ -144,8 +144,7 @@ static int admit(Server *S, Request *r) {
     r->n_combos = binom_u64(r->ds->M, o);
     if (o == 2) {
         r->variant = kF2;
-        const int t = tuned_np_lookup(c, 2, r->ds);
-        r->np = t > 0 && (t != kNpMfma || r->ds->qa) ? t : 4;
+        r->np = default_np2(c, r->ds);
     } else if (o == 3) {
         r->variant = kF3;
         r->np = default_np3(c, r->ds);

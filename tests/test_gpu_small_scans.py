@@ -48,3 +48,24 @@ def test_small_scan_matches_oracle(cx, orc, order, M, N, n_cases, K):
             epi.epi_release(cx.ctx, sid)
     finally:
         epi.epi_unload(cx.ctx, ds)
+
+
+@pytest.mark.parametrize("M,block", [(999, 4), (1000, 16), (1025, 16)])
+def test_order2_default_kernel(cx, M, block):
+    """The untuned order-2 kernel on both sides of its line, against the other
+    one (the same integers, so the same results)."""
+    from paper_2201_02460_amd import epi
+
+    G, y = random_genotypes(M, 321, seed=M, case_fraction=0.4)
+    ds = cx.load(G, y)
+    try:
+        r = cx.scan(ds, 2, 40)
+        assert r["prefix_block"] == block
+        epi.epi_set_prefix_block(cx.ctx, ds, 2, 20 - block)
+        o = cx.scan(ds, 2, 40)
+        assert o["prefix_block"] == 20 - block
+        for k in ("combos", "scores", "tables"):
+            assert np.array_equal(r[k], o[k])
+    finally:
+        epi.epi_set_prefix_block(cx.ctx, ds, 2, 0)
+        epi.epi_unload(cx.ctx, ds)
