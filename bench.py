@@ -242,9 +242,9 @@ def orders_bench(epi, torch, names, steps):
         epi.epi_unload(ctx, ds)
         kms = sorted(mains)[len(mains) // 2]
         # reduced-cell variants count 2^k cells, the generic one all 3^k;
-        # order 2 may run on the matrix cores (2 x 2^2 flops per unit), and
-        # orders 5-8 do (variant 8: 2 x 3^k flops per unit)
-        mfma = info["variant"] == 8 or (order == 2 and info["prefix_block"] == BLOCK_MFMA_FP4)
+        # orders 2 and 4 may run on the matrix cores (variant 9; 2 x 2^k flops
+        # per unit), and orders 5-8 do (variant 8: 2 x 3^k)
+        mfma = info["variant"] in (8, 9) or (order == 2 and info["prefix_block"] == BLOCK_MFMA_FP4)
         flops = 2.0 * 3**order if info["variant"] == 8 else mfma_flops_per_unit(order)
         opu = ops_per_unit(order) if info["variant"] in (1, 2, 5) else ops_per_unit_3k(order)
         out[name] = {"value": work * len(walls) / sum(walls) / 1e12, "kernel_ms": kms,

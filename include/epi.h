@@ -195,7 +195,8 @@ int epi_scan_timing(epi_ctx *ctx, int32_t scan_id, float ms[4]);
 
 /* Number of combinations C(M, order) of a scan and the kernel variant it ran
  * (0 = per-combination generic kernel, 1 = order-2 reduced-cell kernel,
- * 2 = order-3 reduced-cell kernel, 8 = orders 5-8 on the matrix cores) and its
+ * 2 = order-3 reduced-cell kernel, 5 and 9 = order 4 by reduced cells, popcount
+ * and matrix cores, 8 = orders 5-8 on the matrix cores) and its
  * prefix block. */
 int epi_scan_info(epi_ctx *ctx, int32_t scan_id, uint64_t *n_combinations, int32_t *variant,
                   int32_t *prefix_block);

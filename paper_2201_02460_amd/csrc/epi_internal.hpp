@@ -104,12 +104,16 @@ enum Variant : int32_t {
     kF2Fold = 7,   // order 2 scored by the pair sub-table pass of another scan of the same dataset
     kX = 8,        // orders 5-8, all 3^k cells as matrix products of the cell rows of a combination's
                    // first and last SNPs
+    kR4M = 9,      // order 4, reduced cells on the matrix cores, other cells from the sub-tables
 };
+
+constexpr bool is_r4(int variant) { return variant == kR4 || variant == kR4M; }  // reads the triplet sub-table
+constexpr bool is_xgk(int variant) { return variant == kR4M || variant == kX; }  // kernel kXGk + order
 
 // Kernel instantiation of the segmented variant for order k: generic-order
 // parameter kSegGk + k.
 constexpr int kSegGk = 16;
-// ... and of the all-cell matrix-core kernel (kX): kXGk + k.
+// ... and of the matrix-core kernels of order 4 (kR4M) and 5-8 (kX): kXGk + k.
 constexpr int kXGk = 32;
 
 // kX: a combination of order k is a subset of its first xa(k) SNPs (A) and one
@@ -156,8 +160,30 @@ __host__ __device__ inline unsigned long long x_first_group(int k, int M, int l)
 __host__ __device__ inline unsigned long long x_units(int k, int l) {
     return (small_binom(l, xa(k)) + (unsigned)xna(k) - 1) / (unsigned)xna(k);
 }
-// Work items of the groups whose last B subset starts at SNP l.
+// kR4M: a work item is a middle pair j < k with a block ib of 32 first SNPs i
+// and a block lb of 16 last SNPs l.  The items come in groups of one (ib, lb),
+// group lb n_ib + ib, which share the sub-table rows of their i and l: all
+// pairs j < k between the block's first i and last l, k outer, j inner.
+constexpr int kR4I = 32, kR4L = 16;
+__host__ __device__ inline int r4_iblocks(int M) { return (M + kR4I - 1) / kR4I; }
+__host__ __device__ inline int r4_groups(int M) { return r4_iblocks(M) * ((M + kR4L - 1) / kR4L); }
+// values of k in group g: 32 ib + 2 .. min(16 lb + 14, M - 2)
+__host__ __device__ inline int r4_ks(int M, int g) {
+    const int ib = g % r4_iblocks(M), lb = g / r4_iblocks(M), top = kR4L * lb + kR4L - 2;
+    const int n = (top < M - 2 ? top : M - 2) - kR4I * ib - 1;
+    return n > 0 ? n : 0;
+}
+
+// Entries of the first-item table (one more holds the end): order 4 one per
+// group, orders 5-8 one per SNP.
+__host__ __device__ inline int x_entries(int k, int M) { return k == 4 ? r4_groups(M) : M; }
+// Work items of group l (order 4) or of the groups whose last B subset starts
+// at SNP l.
 __host__ __device__ inline unsigned long long x_items(int k, int M, int u, int l) {
+    if (k == 4) {
+        const unsigned long long n = (unsigned)r4_ks(M, l);
+        return n * (n + 1) / 2;
+    }
     return (x_first_group(k, M, l + 1) - x_first_group(k, M, l)) * ((x_units(k, l) + (unsigned)u - 1) / (unsigned)u);
 }
 
@@ -205,13 +231,13 @@ struct Cand {
 struct Task {
     DsView ds;
     uint32_t *pairs;                  // pair sub-table, 8 u32 per pair (lexicographic, or colex: pair_colex)
-    uint32_t *triples;                // colex-ordered triplet sub-table, 8 u32 per triplet (kR4, kF3Emit)
+    uint32_t *triples;                // colex-ordered triplet sub-table, 8 u32 per triplet (kR4, kR4M, kF3Emit)
     const v4u *xrows;                 // kX: cell rows of single SNPs and pairs (layout above)
     uint32_t *seg;                    // kSeg: per wave slot of the launch (4 per workgroup), 2 x 3^k x 64 u32
                                       //   counts, cell-major ([class][cell][lane])
     const unsigned long long *items;  // per-item descriptors: kF3 j<<40 | ib<<20 | mb, kF2 ib<<20 | mb
                                       // (kF3 with np = kNpMfma: 16-SNP i-block ib, 32-SNP m-block mb);
-                                      // kX: the M + 1 first items of each SNP l, see x_items
+                                      // kX, kR4M: the first item of each entry, see x_items
     unsigned long long n_items;
     unsigned long long item_base;     // first global item of this task in its launch
     unsigned long long first_item;    // task-local index of the launch's first item of this task
@@ -265,7 +291,7 @@ struct Task {
 // The host counts a table's items with these functions and the device
 // writes them (items_kernel), group after group.
 enum ItemKind : int32_t { kItemsF2 = 0, kItemsF3 = 1, kItemsF3M = 2, kItemsF3M2 = 3, kItemsF2M = 4,
-                          kItemsX = 16 /* + order: the first item of each SNP l (np: units per item) */ };
+                          kItemsX = 16 /* + order: the first item of each entry (np: units per item) */ };
 constexpr int kItemTile = 4;
 constexpr int kStoreChunkBytes = 1024;  // bytes per store_kernel launch
 

@@ -2519,6 +2519,307 @@ EPI_DEV void item_r4(const Task &t, unsigned long long local, TopK &tk, Cand *li
 }
 
 // ---------------------------------------------------------------------------
+// kR4M: order 4 by reduced cells, the cells counted on the matrix cores.  A
+// work item is a middle pair j < k with 32 first SNPs i (B columns) and 16
+// last SNPs l (A rows, two genotypes each).  The rows of l masked by j's
+// (genotype b) and the columns of i's genotype a masked by k's (genotype c)
+// give eight products a step: three loads feed 24 matrix instructions, both
+// classes in one accumulator (q3_pack_fits).  Lane = SNP i; a lane holds all
+// 16 reduced cells of its i with eight l's, so the scoring is that of kR4: the
+// marginals come from the sub-tables, whose colex order puts consecutive i in
+// consecutive lanes.
+//
+// Bound by the scoring: 81 cells are 243 reads of the screening table, about
+// 1100 LDS cycles per 64 combinations, and some 850 vector instructions, next
+// to 1100 matrix-core cycles (22 blocks of 96 individuals).  M = 200, N = 2000:
+// 4.95 ms, 1.4 of it without the scoring and 3.5 without the table reads,
+// against 7.5 ms for kR4; 0.73 of the lanes hold a combination.  A table of
+// t(n0) + t(n1) - t(n0 + n1) for small counts, one read a cell, was slower
+// (6.9): equal small counts share one read of the plain table.
+// ---------------------------------------------------------------------------
+template <bool CHECK = false, bool PILOT = false>
+EPI_DEV void item_r4m(const Task &t, unsigned long long local, TopK &tk, Cand *list, long long gthr, v4u *stage) {
+    static_assert(!PILOT || !CHECK, "the pilot pass only counts");
+    typedef QFmt<false> Q;
+    const DsView d = t.ds;
+    const int M = d.M, lane = lane_id(), h = lane >> 5;
+    // item -> group (block of i, block of l), then k and j
+    int lo = 0, hi = r4_groups(M) - 1;
+    if (tk.xl <= hi && t.items[tk.xl] <= local && local < t.items[tk.xl + 1]) lo = hi = tk.xl;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (t.items[mid] <= local) lo = mid; else hi = mid - 1;
+    }
+    tk.xl = uni(lo);
+    const int nib = r4_iblocks(M), ib = tk.xl % nib, lb = tk.xl / nib;
+    const unsigned off = (unsigned)(local - t.items[tk.xl]);
+    // k's place r in the group, r (r + 1) / 2 <= off: a root, then corrected
+    unsigned r = (unsigned)((sqrtf(8.0f * (float)off + 1.0f) - 1.0f) * 0.5f);
+    while (r * (r + 1) / 2 > off) --r;
+    while ((r + 1) * (r + 2) / 2 <= off) ++r;
+    const int i0 = kR4I * ib, l0 = kR4L * lb;
+    const int kk = uni(i0 + 2 + (int)r), j = uni(i0 + 1 + (int)(off - r * (r + 1) / 2));
+    const int i = i0 + (lane & 31);
+
+    // Sub-table rows are read through buffer descriptors, so that a lane
+    // without a valid combination reads another entry, or zeros past the
+    // table's end.
+    auto C2 = [](int x) { return (long long)x * (x - 1) / 2; };
+    auto C3 = [](int x) { return (long long)x * (x - 1) * (x - 2) / 6; };
+    auto rows = [](const void *p, long long at, long long end) {
+        const long long left = end - at;
+        return __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)p + at), 0,
+                                                 (int)(left < 0x7fffffffll ? left : 0x7fffffffll), kBufWord3);
+    };
+    const long long t_end = 32 * C3(M), p_end = 16 * C2(M);
+    const __amdgpu_buffer_rsrc_t rTk = rows(t.triples, 32 * (C3(kk) + C2(j) + i0), t_end);
+    const __amdgpu_buffer_rsrc_t rP = rows(t.pairs, 0, p_end);
+    const __amdgpu_buffer_rsrc_t rS = __builtin_amdgcn_make_buffer_rsrc((void *)d.single, 0, d.Mp * 16, kBufWord3);
+
+    const int KS = d.xs, H0 = d.xh0, T = q3_pack_shift(d.ncls[0]), blk = KS * 1024;
+    const v4u *qa = Q::qa(d), *qb = Q::qb(d);
+    auto block = [&](const v4u *q, int b) {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)(q + (long long)b * KS * 64), 0, blk, kBufWord3);
+    };
+    const __amdgpu_buffer_rsrc_t rA = block(qa, lb), rB0 = block(qb, 2 * ib), rB1 = block(qb, 2 * ib + 1);
+    const __amdgpu_buffer_rsrc_t rM[2] = {block(qa, j >> 4), block(qa, kk >> 4)};
+    const int mrow[2] = {j & 15, kk & 15};
+    const int vo = lane * 16;
+    typename Q::acc_t acc[2][2][2];  // [b][c][a]
+    #pragma unroll
+    for (int x = 0; x < 8; ++x) acc[x >> 2][(x >> 1) & 1][x & 1] = (typename Q::acc_t){};
+    // mask rows of j and k staged as those of the two middle SNPs of item_f3m
+    constexpr int kSeg = kQStageSteps;
+    lv4u *slot = (lv4u *)stage;
+    auto stage_masks = [&](int base) __attribute__((always_inline)) {
+        const int n = min(kSeg, KS - base);
+        wave_sync();
+        #pragma unroll
+        for (int jj = 0; jj < 2; ++jj)
+            #pragma unroll
+            for (int e0 = 0; e0 < 4 * kSeg; e0 += kWave) {
+                const int e = min(e0 + lane, 4 * n - 1);
+                const int v = (((e >> 2) * 64) + 32 * ((e >> 1) & 1) + 2 * mrow[jj] + (e & 1)) * 16;
+                slot[jj * 4 * kSeg + e0 + lane] = qload(rM[jj], v, base * 1024);
+            }
+        wave_sync();
+    };
+    struct Ops {
+        v4u a, b0, b1;
+    };
+    auto load = [&](int s) __attribute__((always_inline)) {
+        const int so = min(s, KS - 1) * 1024;
+        return Ops{qload(rA, vo, so), qload(rB0, vo, so), qload(rB1, vo, so)};
+    };
+    int seg = 0;
+    auto mul = [&](int s, const Ops &o, int e) __attribute__((always_inline)) {
+        const int js = 4 * (s - seg) + 2 * h;
+        const v4u J0 = slot[js], J1 = slot[js + 1], K0 = slot[4 * kSeg + js], K1 = slot[4 * kSeg + js + 1];
+        #pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const unsigned pb = plane_bits(p);
+            const int sb = plane_scale(e, p);
+            const v4u A0 = o.a & J0 & pb, A1 = o.a & J1 & pb;
+            #pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int c = x >> 1, a = x & 1;
+                const v4u B = (a ? o.b1 : o.b0) & (c ? K1 : K0) & pb;
+                acc[0][c][a] = Q::mma(A0, B, acc[0][c][a], sb, kScaleA);
+                acc[1][c][a] = Q::mma(A1, B, acc[1][c][a], sb, kScaleA);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    Ops x = load(0);
+    stage_masks(0);
+    #pragma unroll 1
+    for (int s = 0; s < KS; s += 2) {
+        if (s >= seg + kSeg) {
+            seg += kSeg;
+            stage_masks(seg);
+        }
+        const Ops y = load(s + 1);
+        mul(s, x, 2 * s + h >= H0 ? T : 2);
+        __builtin_amdgcn_sched_barrier(0);
+        x = load(s + 2);
+        if (s + 1 < KS) mul(s + 1, y, 2 * s + 2 + h >= H0 ? T : 2);
+    }
+    wave_sync();  // the slot's rows have been read
+
+    auto pack2 = [](unsigned n0, unsigned n1) __attribute__((always_inline)) {
+        return (n0 << kQScaleShift) | (n1 << (16 + kQScaleShift));
+    };
+    const v4u pjk = ((cv4u *)t.pairs)[C2(kk) + j];
+    const v4u sj = ((cv4u *)d.single)[j], sk = ((cv4u *)d.single)[kk];
+    const unsigned nall = pack2((unsigned)d.ncls[0], (unsigned)d.ncls[1]);
+    // triplets with l: from the block's first l on; C(l0 + x, 3) - C(l0, 3) =
+    // x C(l0, 2) + C(x, 2) l0 + C(x, 3)
+    const __amdgpu_buffer_rsrc_t rT = rows(t.triples, 32 * C3(l0), t_end);
+    const int c2l = (int)C2(l0), cj = (int)C2(j) * 32, ck = (int)C2(kk) * 32;
+    int pilot_best = (int)0x80000000u;  // PILOT: the lane's best screening sum
+    int sb = screen_bound(entry_bound(tk, gthr), t.score_const, d.shift, d.tq, 243);
+    // One genotype's 27 cells of a table over three SNPs, in the packed form
+    // of kR4: reduced cells r, pair marginals p (cells of SNPs 1, 2), q (1, 3)
+    // and s (2, 3), single ones x, y, z, all of them n.  Every difference is a
+    // count of its own, so no half goes below zero.
+    auto complete = [](unsigned (&G)[27], const unsigned (&p)[4], const unsigned (&q)[4], const unsigned (&s)[4],
+                       const unsigned (&x)[2], const unsigned (&y)[2], const unsigned (&z)[2], unsigned n)
+                        __attribute__((always_inline)) {
+        unsigned y2[2];  // genotype 2 of SNP 1, f of SNP 2, any of SNP 3
+        #pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            #pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                G[9 * f + 3 * g + 2] = p[2 * f + g] - G[9 * f + 3 * g] - G[9 * f + 3 * g + 1];
+                G[9 * f + 6 + g] = q[2 * f + g] - G[9 * f + g] - G[9 * f + 3 + g];
+            }
+            G[9 * f + 8] = x[f] - p[2 * f] - p[2 * f + 1] - G[9 * f + 6] - G[9 * f + 7];
+            y2[f] = y[f] - p[f] - p[2 + f];
+        }
+        #pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            #pragma unroll
+            for (int g = 0; g < 2; ++g) G[18 + 3 * f + g] = s[2 * f + g] - G[3 * f + g] - G[9 + 3 * f + g];
+            G[18 + 3 * f + 2] = y2[f] - G[18 + 3 * f] - G[18 + 3 * f + 1];
+        }
+        #pragma unroll
+        for (int g = 0; g < 2; ++g) G[24 + g] = z[g] - q[g] - q[2 + g] - G[18 + g] - G[21 + g];
+        G[26] = n - x[0] - x[1] - y2[0] - y2[1] - G[24] - G[25];
+    };
+    const int li = (lane & 31) * 32, cij = (int)C2(j) * 16, cik = (int)C2(kk) * 16;
+    // one loop body for all eight l's of a lane (its code in the instruction
+    // cache, one copy of the exact path): only the accumulators are picked by
+    // a branch
+    #pragma unroll 1
+    for (int u = 0; u < 8; ++u) {
+        const int x0 = 4 * (u >> 1) + (u & 1), x2 = x0 + 2;  // l - l0 in the two lane halves
+        const int l = l0 + x0 + 2 * h;
+        const bool valid = i < j && l > kk && l < M;
+        if (!__ballot(valid)) continue;
+        unsigned W[16];  // the reduced cells 8 a + 4 b + 2 c + e
+        auto pick = [&](auto uc) __attribute__((always_inline)) {
+            constexpr int r0 = 4 * (uc.value >> 1) + 2 * (uc.value & 1);
+            #pragma unroll
+            for (int y = 0; y < 16; ++y)
+                W[y] = __float_as_uint(acc[(y >> 2) & 1][(y >> 1) & 1][y >> 3][r0 + (y & 1)]);
+        };
+        switch (u) {
+        case 0: pick(std::integral_constant<int, 0>{}); break;
+        case 1: pick(std::integral_constant<int, 1>{}); break;
+        case 2: pick(std::integral_constant<int, 2>{}); break;
+        case 3: pick(std::integral_constant<int, 3>{}); break;
+        case 4: pick(std::integral_constant<int, 4>{}); break;
+        case 5: pick(std::integral_constant<int, 5>{}); break;
+        case 6: pick(std::integral_constant<int, 6>{}); break;
+        default: pick(std::integral_constant<int, 7>{}); break;
+        }
+        const int at0 = x0 * c2l + x0 * (x0 - 1) / 2 * l0 + x0 * (x0 - 1) * (x0 - 2) / 6;
+        const int at2 = x2 * c2l + x2 * (x2 - 1) / 2 * l0 + x2 * (x2 - 1) * (x2 - 2) / 6;
+        const int tl = (h ? at2 : at0) * 32, til = tl + i * 32;                                // triplets (., ., l)
+        const int pl = (c2l + x0 * l0 + x0 * (x0 - 1) / 2 + h * (2 * l0 + 2 * x0 + 1)) * 16;  // pairs (., l)
+        bool pass = valid;
+        // The table is built for the screening sum and, for the few that pass,
+        // once more for the exact score: 27 cells of one genotype of i at a
+        // time, so that the registers hold them next to the accumulators.
+        #pragma unroll 1
+        for (int exact = 0; exact < 2; ++exact) {
+            int zero = 0, sh = T;
+            asm volatile("" : "+s"(zero), "+s"(sh));  // (nothing of the loop is kept for the second time)
+            const unsigned m0 = (1u << sh) - 1u;
+            unsigned G[27], R[27];
+            unsigned S = 0;
+            long long num = t.score_const;
+            unsigned long long dig = 0;
+            auto score = [&](auto exact_pass) __attribute__((always_inline)) {
+                if (exact) {
+                    // (one passing combination at a time, a cell per lane)
+                    for (unsigned long long m = __ballot(pass); m; m &= m - 1) {
+                        const int src = __builtin_ctzll(m);
+                        unsigned w = 0;
+                        #pragma unroll
+                        for (int x = 0; x < 27; ++x) {
+                            const unsigned g = (unsigned)__builtin_amdgcn_readlane((int)G[x], src);
+                            w = lane == x ? g : w;
+                        }
+                        const long long sum = wave_sum64(
+                            cell_term_counted(d.tlog, (w & 0xffffu) >> kQScaleShift, w >> (16 + kQScaleShift)));
+                        if (lane == src) num += sum;  // (the spare lanes' terms are 0)
+                    }
+                } else {
+                    if (valid) S += (unsigned)screen_sum_packed<27>(G);
+                    if constexpr (CHECK) {
+                        constexpr int base = 27 * exact_pass.value;
+                        #pragma unroll
+                        for (int x = 0; x < 27; ++x)
+                            dig += (unsigned long long)((G[x] & 0xffffu) >> kQScaleShift) * cell_weight(0, base + x) +
+                                   (unsigned long long)(G[x] >> (16 + kQScaleShift)) * cell_weight(1, base + x);
+                    }
+                }
+            };
+            const v4u pil = qload(rP, pl + i * 16, zero);
+            const v4u pij = qload(rP, i * 16, cij + zero), pik = qload(rP, i * 16, cik + zero);
+            const v4u si = qload(rS, i * 16, zero);
+            auto slab = [&](auto ac) __attribute__((always_inline)) {
+                constexpr int a = ac.value;
+                const v4u jl = qload(rT, til + 16 * a, cj + zero), kl = qload(rT, til + 16 * a, ck + zero);
+                const v4u jk = qload(rTk, li + 16 * a, zero);
+                #pragma unroll
+                for (int y = 0; y < 8; ++y) {
+                    const int b = y >> 2, c = (y >> 1) & 1, e = y & 1;
+                    const unsigned w = W[8 * a + y];
+                    G[9 * b + 3 * c + e] = (w & m0) | ((w >> sh) << (16 + kQScaleShift));
+                }
+                const unsigned p[4] = {jk[0], jk[1], jk[2], jk[3]}, q[4] = {jl[0], jl[1], jl[2], jl[3]};
+                const unsigned s[4] = {kl[0], kl[1], kl[2], kl[3]};
+                const unsigned x[2] = {pij[2 * a], pij[2 * a + 1]}, y[2] = {pik[2 * a], pik[2 * a + 1]};
+                const unsigned z[2] = {pil[2 * a], pil[2 * a + 1]};
+                complete(G, p, q, s, x, y, z, pack2(si[a], si[2 + a]));
+                #pragma unroll
+                for (int v = 0; v < 27; ++v) R[v] = a ? R[v] + G[v] : G[v];
+                score(ac);
+            };
+            slab(std::integral_constant<int, 0>{});
+            __builtin_amdgcn_sched_barrier(0);
+            slab(std::integral_constant<int, 1>{});
+            __builtin_amdgcn_sched_barrier(0);
+            {
+                const v4u k0 = qload(rT, tl, ck + j * 32 + zero), k1 = qload(rT, tl + 16, ck + j * 32 + zero);
+                const v4u sl = qload(rS, l * 16, zero);
+                const v4u pjl = qload(rP, pl, j * 16 + zero), pkl = qload(rP, pl, kk * 16 + zero);
+                #pragma unroll
+                for (int y = 0; y < 8; ++y) G[9 * (y >> 2) + 3 * ((y >> 1) & 1) + (y & 1)] = y < 4 ? k0[y] : k1[y - 4];
+                const unsigned p[4] = {pjk[0], pjk[1], pjk[2], pjk[3]}, q[4] = {pjl[0], pjl[1], pjl[2], pjl[3]};
+                const unsigned s[4] = {pkl[0], pkl[1], pkl[2], pkl[3]};
+                const unsigned x[2] = {pack2(sj[0], sj[2]), pack2(sj[1], sj[3])};
+                const unsigned y[2] = {pack2(sk[0], sk[2]), pack2(sk[1], sk[3])};
+                const unsigned z[2] = {pack2(sl[0], sl[2]), pack2(sl[1], sl[3])};
+                complete(G, p, q, s, x, y, z, nall);
+                #pragma unroll
+                for (int v = 0; v < 27; ++v) G[v] -= R[v];
+                score(std::integral_constant<int, 2>{});
+            }
+            const int cc[4] = {i, j, kk, l};
+            if (exact) {
+                unsigned long long key = 0;
+                #pragma unroll
+                for (int z = 0; z < 4; ++z) key = (key << t.key_bits) | (unsigned long long)cc[z];
+                tk_offer(tk, list, pass, num, key, gthr);
+                sb = screen_bound(entry_bound(tk, gthr), t.score_const, d.shift, d.tq, 243);
+                break;
+            }
+            if constexpr (CHECK) digest_add(tk, valid, combo_hash<4>(cc), dig);
+            if constexpr (PILOT) {
+                if (valid && (int)S > pilot_best) pilot_best = (int)S;
+                break;
+            }
+            pass = valid && (int)S >= sb;
+            if (!__ballot(pass)) break;
+        }
+    }
+    if constexpr (PILOT) pilot_count(tk, t, pilot_best, 243);
+}
+
+// ---------------------------------------------------------------------------
 // Persistent scan kernel: four independent waves per workgroup.  The
 // workgroup pops chunks of work items from a device queue that runs over the
 // concatenated item spaces of all tasks of the launch, in task order; each
@@ -2531,7 +2832,7 @@ EPI_DEV void item_r4(const Task &t, unsigned long long local, TopK &tk, Cand *li
 // matrix cores too) set the floor.
 template <int NP2, int NP3, int GK>
 constexpr int scan_waves_per_eu() {
-    return is_mfma_np(NP3) || NP2 == kNpMfma ? 2
+    return is_mfma_np(NP3) || NP2 == kNpMfma || GK == kXGk + 4 ? 2
                            : (GK >= 4 ? 2 : (GK == 3 ? 3 : (NP3 >= 8 ? 2 : (NP3 >= 4 ? 3 : (NP3 >= 2 ? 4 : (NP2 >= 8 ? 3 : 4))))));
 }
 
@@ -2610,7 +2911,7 @@ scan_persistent(const Task *__restrict__ tasks, int n_tasks, unsigned long long 
             // it fits
             const int ent_fwd = T0.ds.N + 1, ent_rev = 2 * T0.ds.N + 2;
             const bool want = (T0.variant == kF2 || T0.variant == kF2Fold || T0.variant == kF3 || T0.variant == kR4 ||
-                               T0.variant == kX) &&
+                               T0.variant == kR4M || T0.variant == kX) &&
                               ent_fwd <= tab_cap &&
                               (unsigned)(uintptr_t)(lu32 *)s_tab == 0u;
             const bool sgn = T0.variant == kF3 && is_mfma_np(T0.np);
@@ -2735,8 +3036,12 @@ scan_persistent(const Task *__restrict__ tasks, int n_tasks, unsigned long long 
                 break;
             case kX:
                 // (the host takes it only where the table fits the LDS)
-                if constexpr (GK > kXGk)
+                if constexpr (GK > kXGk + 4)
                     if (lds) item_x<GK - kXGk, CHECK>(T, local, tk, s_list, gthr);
+                break;
+            case kR4M:
+                if constexpr (GK == kXGk + 4)
+                    if (lds) item_r4m<CHECK>(T, local, tk, s_list, gthr, s_stage);
                 break;
             case kSeg:
                 if constexpr (GK > kSegGk && GK < kXGk) {
@@ -2805,6 +3110,7 @@ struct ScanKernelEntry {
         {0, 0, kSegGk + 6, scan_persistent<0, 0, kSegGk + 6, CK>},                                                 \
         {0, 0, kSegGk + 7, scan_persistent<0, 0, kSegGk + 7, CK>},                                                 \
         {0, 0, kSegGk + 8, scan_persistent<0, 0, kSegGk + 8, CK>},                                                 \
+        {0, 0, kXGk + 4, scan_persistent<0, 0, kXGk + 4, CK>}, /* order 4 on the matrix cores */                 \
         {0, 0, kXGk + 5, scan_persistent<0, 0, kXGk + 5, CK>}, /* all cells on the matrix cores */               \
         {0, 0, kXGk + 6, scan_persistent<0, 0, kXGk + 6, CK>},                                                     \
         {0, 0, kXGk + 7, scan_persistent<0, 0, kXGk + 7, CK>},                                                     \
@@ -2897,7 +3203,9 @@ scan_pilot(const Task *__restrict__ tasks, int n_tasks, unsigned long long total
         tk.top = -1;
         tk.added = 0;
         if (ent_fwd <= tab_cap && local < T.n_items) {
-            if constexpr (GK > kXGk) {
+            if constexpr (GK == kXGk + 4) {
+                item_r4m<false, true>(T, local, tk, s_list, none, s_stage);
+            } else if constexpr (GK > kXGk) {
                 item_x<GK - kXGk, false, true>(T, local, tk, s_list, none);
             } else if constexpr (GK == 4) {
                 item_r4<true, false, true>(T, local, tk, s_list, none, binom, bstride);
@@ -3663,15 +3971,17 @@ __global__ void __launch_bounds__(1024) items_kernel(int kind, int M, int np, un
     }
 }
 
-// kX: first work item of each SNP l = 0 .. M (x_items summed), one workgroup.
+// kX, kR4M: first work item of each entry and the end (x_items summed), one
+// workgroup.
 __global__ void __launch_bounds__(1024) xbase_kernel(int order, int M, int u, unsigned long long *__restrict__ out) {
     __shared__ unsigned long long s_scan[1024];
     __shared__ unsigned long long s_base;
     if (threadIdx.x == 0) s_base = 0;
     __syncthreads();
-    for (int l0 = 0; l0 <= M; l0 += 1024) {
+    const int L = x_entries(order, M);
+    for (int l0 = 0; l0 <= L; l0 += 1024) {
         const int l = l0 + (int)threadIdx.x;
-        const unsigned long long n = l < M ? x_items(order, M, u, l) : 0ull;
+        const unsigned long long n = l < L ? x_items(order, M, u, l) : 0ull;
         s_scan[threadIdx.x] = n;
         __syncthreads();
         for (int off = 1; off < 1024; off <<= 1) {
@@ -3680,7 +3990,7 @@ __global__ void __launch_bounds__(1024) xbase_kernel(int order, int M, int u, un
             s_scan[threadIdx.x] += v;
             __syncthreads();
         }
-        if (l <= M) out[l] = s_base + s_scan[threadIdx.x] - n;
+        if (l <= L) out[l] = s_base + s_scan[threadIdx.x] - n;
         __syncthreads();
         if (threadIdx.x == 1023) s_base += s_scan[1023];
         __syncthreads();
@@ -3765,6 +4075,7 @@ hipError_t launch_pilot(int np2, int np3, int gk, int grid, hipStream_t st, cons
                         int stage_cap) {
     void (*fn)(const Task *, int, unsigned long long, const unsigned long long *, int, int, int, int) =
         gk == 4               ? scan_pilot<0, 0, 4>
+        : gk == kXGk + 4      ? scan_pilot<0, 0, kXGk + 4>
         : gk == kXGk + 5      ? scan_pilot<0, 0, kXGk + 5>
         : gk == kXGk + 6      ? scan_pilot<0, 0, kXGk + 6>
         : gk == kXGk + 7      ? scan_pilot<0, 0, kXGk + 7>

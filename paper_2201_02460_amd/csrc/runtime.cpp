@@ -433,7 +433,7 @@ static int tuned_np(Ctx *c, int order, const Dataset *d) {
 // layouts in epi_internal.hpp (item_group); the device writes the tables
 // (items_kernel) and the host only counts their items.
 static int item_kind(int variant, int np) {
-    if (variant > kXGk) return kItemsX + (variant - kXGk);  // (kX tables are cached as variant kXGk + order)
+    if (variant > kXGk) return kItemsX + (variant - kXGk);  // (kX and kR4M tables are cached as kXGk + order)
     if (variant != kF3) return np == kNpMfma ? kItemsF2M : kItemsF2;
     if (np == kNpMfma2) return kItemsF3M2;
     return is_mfma_np(np) ? kItemsF3M : kItemsF3;
@@ -442,7 +442,7 @@ static int item_kind(int variant, int np) {
 static unsigned long long item_count(int kind, int M, int np) {
     unsigned long long n = 0;
     if (kind >= kItemsX) {
-        for (int l = 0; l < M; ++l) n += x_items(kind - kItemsX, M, np, l);
+        for (int l = 0; l < x_entries(kind - kItemsX, M); ++l) n += x_items(kind - kItemsX, M, np, l);
         return n;
     }
     const long long G = item_groups(kind, M, np);
@@ -450,9 +450,10 @@ static unsigned long long item_count(int kind, int M, int np) {
     return n;
 }
 
-// Bytes of a descriptor table of n items (kX: one entry per SNP and one past).
+// Bytes of a descriptor table of n items (kX, kR4M: the entries' first items
+// and the end).
 static size_t item_bytes(int kind, int M, unsigned long long n) {
-    return (kind >= kItemsX ? (size_t)M + 1 : (size_t)std::max<unsigned long long>(n, 1)) * 8;
+    return (kind >= kItemsX ? (size_t)x_entries(kind - kItemsX, M) + 1 : (size_t)std::max<unsigned long long>(n, 1)) * 8;
 }
 
 // Descriptor table of a shape, built once per context and cached.
@@ -674,7 +675,7 @@ int default_np3(Ctx *c, const Dataset *d) {
 // at N = 4000 takes 166 us without and 156 with, at N = 9483 152 and 162, but
 // M = 600 (780 items) at N = 8000 401 and 171.
 int pilot_items_for(int variant, int np, unsigned long long n_items, int top_k, int N, int tab_cap, int waves) {
-    if (!((variant == kF3 && is_mfma_np(np)) || variant == kR4 || variant == kF2 || variant == kX) || tab_cap < N + 1) return 0;
+    if (!((variant == kF3 && is_mfma_np(np)) || variant == kR4 || variant == kR4M || variant == kF2 || variant == kX) || tab_cap < N + 1) return 0;
     if (variant == kF2 && n_items <= 256 && N > 6000) return 0;
     const unsigned long long want = std::max<unsigned long long>(n_items / 32, 4ull * std::max(top_k, 1));
     const unsigned long long n = std::min({(unsigned long long)waves, n_items, want});
@@ -743,8 +744,9 @@ int grid_for(Ctx *c, int np2, int np3, int gk, unsigned long long items, int tab
 // prefix SNP (order 2: NP SNPs, order 3: NP + 1) times the words of one chunk
 // (at most 16 groups of 4 words, 2048 individuals of a class, which keeps
 // three 4-wave workgroups per CU next to an 8001-entry screening table).
-int stage_cap_for(int np2, int np3, int w4_max) {
+int stage_cap_for(int np2, int np3, int w4_max, int gk) {
     if (np2 == kNpMfma) return 0;  // order 2 on the matrix cores stages nothing
+    if (gk == kXGk + 4) return 8 * kQStageSteps;  // both middle SNPs' mask rows
     if (np3 == kNpMfma2) return 8 * kQStageSteps;  // two middle SNPs' mask rows: 4 entries per step each
     if (np3 == kNpMfmaI8) return 4 * kQ8StageSteps;
     if (is_mfma_np(np3)) return 4 * kQStageSteps;  // j-mask rows: 4 entries per step
@@ -757,7 +759,7 @@ int stage_cap_for(int np2, int np3, int w4_max) {
 // signed cell form, layout in epi_internal.hpp).
 void set_pair_form(Task &t, const Dataset *d, int order, int variant, int np) {
     const bool q3 = order == 3 && is_mfma_np(np);
-    const bool r4 = variant == kR4;
+    const bool r4 = is_r4(variant);
     t.cell_shift = q3 ? kQScaleShift : 0;
     t.cell_bias = q3 ? q3_bias(d->N) : 0u;
     t.cell_neg = q3 ? 1 : 0;
@@ -767,7 +769,7 @@ void set_pair_form(Task &t, const Dataset *d, int order, int variant, int np) {
 // Bytes of a scan's pair sub-table (order 4 by reduced cells: 16 per pair,
 // both classes of a cell in one word; else 32) and triplet sub-table (32 per
 // triplet, both classes in one word).
-uint64_t pair_table_bytes(int variant, int M) { return binom_u64(M, 2) * (variant == kR4 ? 16 : 32); }
+uint64_t pair_table_bytes(int variant, int M) { return binom_u64(M, 2) * (is_r4(variant) ? 16 : 32); }
 uint64_t triple_table_bytes(int M) { return binom_u64(M, 3) * 32; }
 
 // Screening-table entries a scan takes in LDS: the first half (N + 1) when
@@ -778,7 +780,7 @@ uint64_t triple_table_bytes(int M) { return binom_u64(M, 3) * 32; }
 int tab_entries_for(const Dataset *d, int variant, int np, bool both) {
     if (variant == kGeneric || variant == kSeg)  // exact int64 table, n = 0 .. N
         return 2 * (d->N + 1) <= Plan::kTabMax ? 2 * (d->N + 1) : 0;
-    if (variant != kF2 && variant != kF3 && variant != kR4 && variant != kX) return 0;
+    if (variant != kF2 && variant != kF3 && !is_r4(variant) && variant != kX) return 0;
     const bool sgn = variant == kF3 && is_mfma_np(np);
     if (both && sgn && 2 * d->N + 2 <= Plan::kTabMax) return 2 * d->N + 2;
     return d->N + 1 <= Plan::kTabMax ? d->N + 1 : 0;
@@ -795,8 +797,8 @@ int tab_entries_for(const Dataset *d, int variant, int np, bool both) {
 // they do not lower the occupancy of the others.
 bool table_lowers_occupancy(const Dataset *d, int variant, int np, int order, int top_k) {
     const int np2 = order == 2 ? np : 0, np3 = order == 3 ? np : 0,
-              gk = order >= 4 ? (variant == kX ? kXGk : 0) + order : 0;
-    const int stage = stage_cap_for(np2, np3, std::max(d->w4[0], d->w4[1]));
+              gk = order >= 4 ? (is_xgk(variant) ? kXGk : 0) + order : 0;
+    const int stage = stage_cap_for(np2, np3, std::max(d->w4[0], d->w4[1]), gk);
     const int ent = tab_entries_for(d, variant, np, false);
     return ent > 0 && wgs_per_cu(np2, np3, gk, ent, top_k, stage) < wgs_per_cu(np2, np3, gk, 0, top_k, stage);
 }
@@ -811,11 +813,11 @@ int group_tab_cap(int np2, int np3, int gk, int cap_both, int cap_first, int kma
 static void pick_tab_cap(const Plan *p, LaunchGroup &g) {
     int cap_both = 0, cap_first = 0;
     g.kmax = 1;
-    g.stage_cap = stage_cap_for(g.np2, g.np3, 0);
+    g.stage_cap = stage_cap_for(g.np2, g.np3, 0, g.gk);
     for (int i : g.scans) {
         const PlanScan &s = p->scans[i];
         g.kmax = std::max(g.kmax, s.desc.top_k);
-        g.stage_cap = std::max(g.stage_cap, stage_cap_for(g.np2, g.np3, std::max(s.ds->w4[0], s.ds->w4[1])));
+        g.stage_cap = std::max(g.stage_cap, stage_cap_for(g.np2, g.np3, std::max(s.ds->w4[0], s.ds->w4[1]), g.gk));
         cap_both = std::max(cap_both, tab_entries_for(s.ds, s.variant, s.np, true));
         cap_first = std::max(cap_first, tab_entries_for(s.ds, s.variant, s.np, false));
     }
@@ -834,6 +836,20 @@ bool r4_fits(const Dataset *d) {
 // Order 4 runs by reduced cells when they fit, unless the all-cell kernel is
 // pinned for the dataset's size bucket.
 bool use_r4(Ctx *c, const Dataset *d) { return r4_fits(d) && tuned_np_lookup(c, 4, d) != EPI_BLOCK_ALL_CELLS; }
+
+// ... with the cells counted on the matrix cores (kR4M) where both classes fit
+// one accumulator and the screening table leaves two workgroups a CU their
+// LDS.  Its cost hardly depends on N, that of kR4 is linear in it, and kR4M's
+// blocks of 32 x 16 SNPs fill with M.  A scan, kR4 and kR4M: M = 200 at N =
+// 2000 7.6 and 5.1 ms, at N = 500 4.5 both; M = 300, N = 300 21.6 and 18.2;
+// M = 150, N = 1000 2.06 and 1.98, N = 300 1.66 and 1.89; M = 100, N = 4000
+// 1.00 and 0.78, N = 2000 0.69 and 0.73.  With one block of first SNPs the
+// few long items of kR4 leave the chip idle: M = 24, N = 300 223 and 176 us,
+// M = 32, N = 2000 278 and 222, but M = 34, N = 300 230 and 274.
+static bool r4m_fits(const Dataset *d) {
+    return r4_fits(d) && q3_pack_fits(d->n_case, d->n_ctrl) && d->N <= 8191 &&
+           (d->M <= kR4I || (long long)(d->M - 50) * d->N >= 130000);
+}
 
 // Orders 5-8 count all cells on the matrix cores (kX) where both classes fit
 // one float accumulator (x_pack_fits: up to 4095 individuals a class), the
@@ -860,7 +876,7 @@ static int x_units_per_item(Ctx *c, int order, unsigned long long n_combos) {
 }
 
 static bool needs_pairs(const PlanScan &s) {
-    return s.variant != kSeg && (s.desc.order == 3 || s.variant == kR4);
+    return s.variant != kSeg && (s.desc.order == 3 || is_r4(s.variant));
 }
 
 int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool graph, Plan **out,
@@ -912,6 +928,11 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
             else if (force_np != kForceReducedCells) r4 = r4 && use_r4(c, s.ds);
             s.variant = r4 ? kR4 : kGeneric;
             s.np = kGenRanksHost;
+            if (r4 && r4m_fits(s.ds)) {
+                s.variant = kR4M;
+                if ((rc = plan_items(c, p.get(), kXGk + 4, s.ds->M, 0, &s.items, &s.n_items))) return cleanup(rc);
+                continue;
+            }
             if (x_fits(s.ds, o) && (!arena || x_bytes(s.ds) <= arena->cap / 2)) {
                 // without room for its operand rows the scan takes the
                 // per-combination kernel
@@ -957,7 +978,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
             if (s.variant == kF2Fold) continue;  // runs in the pair pass
             const bool seg = s.variant == kSeg;
             int key = seg ? 200 + s.desc.order : group_of_order(s.desc.order, s.np);
-            if (s.variant == kX) key = 300 + s.desc.order;
+            if (is_xgk(s.variant)) key = 300 + s.desc.order;
             if (!seg && table_lowers_occupancy(s.ds, s.variant, s.np, s.desc.order, s.desc.top_k)) key += 100;
             LaunchGroup &g = by_key[key];
             g.scans.push_back(i);
@@ -967,7 +988,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
                 g.np2 = g.np3 = 0;
                 g.gk = kSegGk + s.desc.order;
             }
-            if (s.variant == kX) g.gk = kXGk + s.desc.order;
+            if (is_xgk(s.variant)) g.gk = kXGk + s.desc.order;
         }
         for (auto &kv : by_key) p->groups.push_back(kv.second);
     } else {
@@ -989,7 +1010,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
             } else {
                 g.np2 = 0;
                 g.np3 = 0;
-                g.gk = (s.variant == kX ? kXGk : 0) + s.desc.order;
+                g.gk = (is_xgk(s.variant) ? kXGk : 0) + s.desc.order;
             }
             g.scans.push_back(i);
             p->groups.push_back(g);
@@ -1007,7 +1028,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
             const size_t pb = (size_t)pair_table_bytes(s.variant, s.ds->M);
             if ((rc = plan_alloc(c, p.get(), std::max<size_t>(pb, 32), &s.pairs))) return cleanup(rc);
         }
-        if (s.variant == kR4) {
+        if (is_r4(s.variant)) {
             if ((rc = plan_items(c, p.get(), kF3, s.ds->M, kNpMfma, &s.t3_items_d, &s.t3_items))) return cleanup(rc);
             const size_t tb = (size_t)triple_table_bytes(s.ds->M);
             if ((rc = plan_alloc(c, p.get(), std::max<size_t>(tb, 64), &s.triples))) return cleanup(rc);
@@ -1018,7 +1039,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
     int n_emit = 0, n_t3 = 0;
     for (auto &s : p->scans) {
         n_emit += needs_pairs(s) ? 1 : 0;
-        n_t3 += s.variant == kR4 ? 1 : 0;
+        n_t3 += is_r4(s.variant) ? 1 : 0;
     }
     p->n_emit = n_emit;
     p->n_t3 = n_t3;
@@ -1036,7 +1057,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
     unsigned long long emit_total = 0, t3_total = 0;
     for (auto &s : p->scans) {
         emit_total += needs_pairs(s) ? s.emit_items : 0;
-        t3_total += s.variant == kR4 ? s.t3_items : 0;
+        t3_total += is_r4(s.variant) ? s.t3_items : 0;
     }
     int emit_w4 = 1;
     for (auto &s : p->scans)
@@ -1171,7 +1192,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
         base = 0;
         for (int i = 0; i < nt; ++i) {
             PlanScan &s = p->scans[i];
-            if (s.variant != kR4) continue;
+            if (!is_r4(s.variant)) continue;
             s.t3_task = e;
             Task &t = tasks[e++];
             t = tasks[i];
@@ -1292,7 +1313,7 @@ static int plan_enqueue(Ctx *c, Plan *p, hipStream_t st, bool timing, unsigned l
                                    c->d_binom, c->bstride, 0, 1, es));
                 HIPCHK(launch_init_counters(st, p->d_queues, 1, nullptr, nullptr, 0, nullptr));
             }
-            if (s.variant == kR4) {
+            if (is_r4(s.variant)) {
                 const int ts = stage_cap_for(0, kNpMfma, 0);
                 const int tg = grid_for(c, 0, kNpMfma, 0, s.t3_items, 0, 1, ts);
                 HIPCHK(launch_scan(0, kNpMfma, 0, tg, st, tasks + s.t3_task, 1, s.t3_items, p->d_queues + 0,
@@ -1461,6 +1482,21 @@ static unsigned long long valid_in_items(const PlanScan &s, unsigned long long a
                 }
             }
             base += items;
+        }
+        return n;
+    }
+    if (s.variant == kR4M) {
+        unsigned long long n = 0, base = 0;
+        for (int g = 0; g < r4_groups((int)M) && base < b; ++g) {
+            const long long items = (long long)x_items(4, (int)M, 0, g);
+            const long long i0 = (long long)kR4I * (g % r4_iblocks((int)M)), l0 = (long long)kR4L * (g / r4_iblocks((int)M));
+            long long at = (long long)base;
+            for (long long k = i0 + 2; k < i0 + 2 + r4_ks((int)M, g); ++k)
+                for (long long j = i0 + 1; j < k; ++j, ++at)
+                    if (at >= (long long)a && at < (long long)b)
+                        n += (unsigned long long)((std::min(j, i0 + kR4I) - i0) *
+                                                  std::max(0ll, std::min(M, l0 + kR4L) - std::max(k + 1, l0)));
+            base += (unsigned long long)items;
         }
         return n;
     }

@@ -249,7 +249,7 @@ int default_np3(Ctx *c, const Dataset *d);
 bool np3_usable(const Dataset *d, int np);
 int np3_group_inst(int np3, int n, int n_pack);
 int grid_for(Ctx *c, int np2, int np3, int gk, unsigned long long items, int tab_cap, int kmax, int stage_cap);
-int stage_cap_for(int np2, int np3, int w4_max);
+int stage_cap_for(int np2, int np3, int w4_max, int gk = 0);
 int tab_entries_for(const Dataset *d, int variant, int np, bool both);
 void set_pair_form(Task &t, const Dataset *d, int order, int variant, int np);
 int group_tab_cap(int np2, int np3, int gk, int cap_both, int cap_first, int kmax, int stage_cap);
