@@ -3677,47 +3677,69 @@ hipError_t launch_function(int fn, int order, hipStream_t st, const DsView &d, c
 }
 
 // ---------------------------------------------------------------------------
-// Packing (Section 2.1): one thread per (SNP, 128-individual group of a
-// class).  idx lists the input position of each class's individuals (cases
-// first).  Genotypes outside {0,1,2} raise *err.
+// Packing (Section 2.1): a wave takes kPackSnps SNPs of one 128-individual
+// group of a class.  idx lists the input position of each class's individuals
+// (cases first, in input order), so a SNP's 64 genotypes of a load lie close
+// together, and a ballot over the wave is two words of its row.  Genotypes
+// outside {0,1,2} raise *err.
+//
+// Bound by the latency of the byte loads, which go eight at a time: M = 1000,
+// N = 4000 43 us with a thread per SNP and group (each byte of a row another
+// load of the same thread, a line per lane), now 8; M = 4000 82 and 19.
 // ---------------------------------------------------------------------------
-__global__ void pack_kernel(const uint8_t *__restrict__ geno, long long ld, const int32_t *__restrict__ idx, DsView d,
-                            v4u *__restrict__ masks, int *__restrict__ err) {
-    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int G4 = d.w4[0] + d.w4[1];
-    if (tid >= (long long)G4 * d.Mp) return;
-    const int s = (int)(tid % d.Mp);
-    const int g4 = (int)(tid / d.Mp);
+constexpr int kPackSnps = 16;
+__global__ void __launch_bounds__(256) pack_kernel(const uint8_t *__restrict__ geno, long long ld,
+                                                   const int32_t *__restrict__ idx, DsView d,
+                                                   v4u *__restrict__ masks, int *__restrict__ err) {
+    const int nsb = (d.Mp + kPackSnps - 1) / kPackSnps;
+    const long long wid = (long long)blockIdx.x * 4 + uni((int)(threadIdx.x >> 6));
+    if (wid >= (long long)(d.w4[0] + d.w4[1]) * nsb) return;
+    const int g4 = uni((int)(wid / nsb)), s0 = uni((int)(wid % nsb)) * kPackSnps, lane = lane_id();
     const int cl = g4 < d.w4[0] ? 0 : 1;
-    const int w4 = g4 - d.wbase[cl];
     const int32_t *cidx = idx + (cl == 0 ? 0 : d.ncls[0]);
-    v4u r0 = {0u, 0u, 0u, 0u}, r1 = {0u, 0u, 0u, 0u};
     int bad = 0;
-    if (s < d.M) {
-        const uint8_t *row = geno + (long long)s * ld;
-        #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            unsigned b0 = 0, b1 = 0;
-            for (int b = 0; b < 32; ++b) {
-                const int pos = 32 * (4 * w4 + q) + b;
-                if (pos < d.ncls[cl]) {
-                    const unsigned si = (unsigned)cidx[pos];
-                    if (si >= (unsigned)d.N) {
-                        bad |= 8;
-                        continue;
-                    }
-                    const unsigned g = row[si];
-                    b0 |= (g == 0u ? 1u : 0u) << b;
-                    b1 |= (g == 1u ? 1u : 0u) << b;
-                    bad |= g > 2u ? 1 : 0;
-                }
-            }
-            r0[q] = b0;
-            r1[q] = b1;
+    unsigned at[2];
+    bool in[2];
+    #pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int pos = 128 * (g4 - d.wbase[cl]) + 64 * q + lane;
+        in[q] = pos < d.ncls[cl];
+        at[q] = in[q] ? (unsigned)cidx[pos] : 0u;
+        if (at[q] >= (unsigned)d.N) {
+            bad |= 8;
+            in[q] = false;
+            at[q] = 0;
         }
     }
-    masks[((long long)g4 * 2 + 0) * d.Mp + s] = r0;
-    masks[((long long)g4 * 2 + 1) * d.Mp + s] = r1;
+    v4u r0 = {0u, 0u, 0u, 0u}, r1 = {0u, 0u, 0u, 0u};
+    #pragma unroll
+    for (int x0 = 0; x0 < kPackSnps; x0 += 4) {
+        unsigned g[4][2];
+        #pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const uint8_t *row = geno + (long long)min(s0 + x0 + x, d.M - 1) * ld;
+            g[x][0] = row[at[0]];
+            g[x][1] = row[at[1]];
+        }
+        #pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const bool real = s0 + x0 + x < d.M, mine = lane == x0 + x;  // (rows past the last SNP are zero)
+            #pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const bool v = real && in[q];
+                const unsigned long long b0 = __ballot(v && g[x][q] == 0u), b1 = __ballot(v && g[x][q] == 1u);
+                bad |= v && g[x][q] > 2u ? 1 : 0;
+                r0[2 * q] = mine ? (unsigned)b0 : r0[2 * q];
+                r0[2 * q + 1] = mine ? (unsigned)(b0 >> 32) : r0[2 * q + 1];
+                r1[2 * q] = mine ? (unsigned)b1 : r1[2 * q];
+                r1[2 * q + 1] = mine ? (unsigned)(b1 >> 32) : r1[2 * q + 1];
+            }
+        }
+    }
+    if (lane < kPackSnps && s0 + lane < d.Mp) {
+        masks[((long long)g4 * 2 + 0) * d.Mp + s0 + lane] = r0;
+        masks[((long long)g4 * 2 + 1) * d.Mp + s0 + lane] = r1;
+    }
     if (bad) atomicOr(err, bad);
 }
 
@@ -3886,15 +3908,12 @@ __global__ void qpack8_kernel(DsView d, v4u *__restrict__ qa8, v4u *__restrict__
 // other than n_case bit 4 (some index then falls outside its class).
 __global__ void __launch_bounds__(1024) classidx_kernel(const uint8_t *__restrict__ pheno, int N, int n_case,
                                                         int32_t *__restrict__ idx, int *__restrict__ err) {
-    __shared__ int s_scan[1024];
-    __shared__ int s_cases;
-    const int tid = threadIdx.x;
-    if (tid == 0) {
-        s_cases = 0;
-        *err = 0;
-    }
+    __shared__ int s_wave[2][16];  // cases of each wave of a chunk, two chunks in turn
+    const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
+    if (tid == 0) *err = 0;
     __syncthreads();
-    for (int base = 0; base < N; base += 1024) {
+    int bc = 0;  // cases before the chunk
+    for (int base = 0, k = 0; base < N; base += 1024, k ^= 1) {
         const int s = base + tid;
         int f = 0;
         if (s < N) {
@@ -3902,16 +3921,16 @@ __global__ void __launch_bounds__(1024) classidx_kernel(const uint8_t *__restric
             f = v == 1u ? 1 : 0;
             if (v > 1u) atomicOr(err, 2);
         }
-        s_scan[tid] = f;
+        const unsigned long long m = __ballot(f);
+        if (lane == 0) s_wave[k][wave] = (int)__popcll(m);
         __syncthreads();
-        for (int off = 1; off < 1024; off <<= 1) {
-            const int v = tid >= off ? s_scan[tid - off] : 0;
-            __syncthreads();
-            s_scan[tid] += v;
-            __syncthreads();
+        int before = (int)lane_prefix(m), all = 0;  // cases before s within the chunk, all of them
+        #pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int n = s_wave[k][w];
+            before += w < wave ? n : 0;
+            all += n;
         }
-        const int before = s_scan[tid] - f;  // cases before s within this chunk
-        const int bc = s_cases;
         if (s < N) {
             if (f) {
                 if (bc + before < n_case) idx[bc + before] = s;
@@ -3922,9 +3941,7 @@ __global__ void __launch_bounds__(1024) classidx_kernel(const uint8_t *__restric
                 else atomicOr(err, 4);
             }
         }
-        __syncthreads();
-        if (tid == 1023) s_cases = bc + s_scan[1023];
-        __syncthreads();
+        bc += all;
     }
 }
 
@@ -4175,8 +4192,8 @@ hipError_t launch_reseed(int n_tasks, hipStream_t st, const Task *tasks, const C
 
 hipError_t launch_pack(hipStream_t st, const uint8_t *geno, long long ld, const int32_t *idx, const DsView &d,
                        v4u *masks, int *err) {
-    const long long n = (long long)(d.w4[0] + d.w4[1]) * d.Mp;
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, geno, ld, idx, d, masks, err);
+    const long long n = (long long)(d.w4[0] + d.w4[1]) * ((d.Mp + kPackSnps - 1) / kPackSnps);  // waves
+    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, geno, ld, idx, d, masks, err);
     return hipGetLastError();
 }
 
