@@ -3371,9 +3371,10 @@ __global__ void __launch_bounds__(1024) merge_final_kernel(const Task *__restric
 // 2 = valid & ~(row0 | row1)) in LDS, kFinWords 128-individual words at a
 // time; the threads that share a cell (tables of fewer than 256 cells) take
 // every parts-th word of it and add their counts in LDS.  One wave that
-// walked all cells of a result from global memory left the device idle: 2.6
-// ms for the ten 6561-cell tables of an order-8 scan, now 0.03; 81 us for a
-// hundred of order 5, 25 for order 3 at N = 4000.
+// walked all cells of a result from global memory left the device idle: 2600
+// us for the ten 6561-cell tables of an order-8 scan, now 14; a hundred of
+// order 5 81 and 11, of order 4 36 and 7, of order 3 at N = 4000 25 and 8.
+// Bound by the latency of its few loads.
 // ---------------------------------------------------------------------------
 constexpr int kFinThreads = 256, kFinWords = 16;
 
@@ -3550,46 +3551,120 @@ __global__ void __launch_bounds__(256) gt_kernel(DsView d, const int32_t *__rest
     }
 }
 
-// One thread per combination: its 2 x 3^K counts, tables[i][class][x].
+// Both classes' 3^K cells of combination c (K = 2, 3).
 template <int K>
-__global__ void __launch_bounds__(256) ct_kernel(DsView d, const int32_t *__restrict__ combos, unsigned long long n,
-                                                 uint32_t *__restrict__ tables, int *__restrict__ err) {
-    for (unsigned long long i = blockIdx.x * 256ull + threadIdx.x; i < n; i += (unsigned long long)gridDim.x * 256ull) {
+EPI_DEV void count_small(const DsView &d, const int (&c)[K], unsigned (&acc)[2 * pow3c(K)]) {
+    constexpr int P = pow3c(K);
+    gv4u *gm = (gv4u *)d.masks;
+    #pragma unroll
+    for (int cl = 0; cl < 2; ++cl) {
+        #pragma unroll
+        for (int x = 0; x < P; ++x) acc[cl * P + x] = 0;
+        long long off = (long long)d.wbase[cl] * 2 * d.Mp;
+        for (int w = 0; w < d.w4[cl]; ++w, off += 2 * d.Mp) {
+            const v4u vm = valid_mask(d.ncls[cl], w);
+            v4u r[K][3];
+            #pragma unroll
+            for (int u = 0; u < K; ++u) {
+                r[u][0] = gm[off + c[u]];
+                r[u][1] = gm[off + d.Mp + c[u]];
+                r[u][2] = vm & ~(r[u][0] | r[u][1]);
+            }
+            #pragma unroll
+            for (int q = 0; q < 4; ++q)
+                #pragma unroll
+                for (int x = 0; x < P; ++x) {
+                    const int g0 = x / (P / 3), g1 = x / (P / 9) % 3, g2 = x % 3;
+                    unsigned v = r[0][g0][q] & r[1][g1][q];
+                    if constexpr (K == 3) v &= r[K - 1][g2][q];
+                    acc[cl * P + x] = bcnt_acc(v, acc[cl * P + x]);
+                }
+        }
+    }
+}
+
+// Contingency tables, tables[i][class][x]: a one-wave workgroup takes 64
+// combinations, one per lane, and (orders 4 up) one class and 81 cells of
+// their tables; the counts go through LDS, half the lanes at a time, so that
+// the stores are runs of whole table parts.  Bound by the counting's vector
+// instructions; 100000 combinations of order 4, N = 2048: 92 us with a
+// thread per table (three passes over the rows, every lane of a store in a
+// line of its own), now 63.
+template <int K>
+constexpr int ct_units() { return K < 4 ? 1 : 2 * pow3c(K > 4 ? K - 4 : 0); }
+template <int K>
+__global__ void __launch_bounds__(64) ct_kernel(DsView d, const int32_t *__restrict__ combos, unsigned long long n,
+                                                uint32_t *__restrict__ tables, int *__restrict__ err) {
+    constexpr int U = ct_units<K>(), C = K < 4 ? 2 * pow3c(K) : 81, ROW = C | 1;  // an odd stride
+    __shared__ unsigned slot[32 * ROW];
+    const int lane = threadIdx.x;
+    const unsigned long long units = (n + 63) / 64 * U;
+    for (unsigned long long id = blockIdx.x; id < units; id += gridDim.x) {
+        const unsigned long long i0 = id / U * 64;
+        const int sub = (int)(id % U), cl = sub & 1, gi = sub >> 1;
+        const bool live = i0 + lane < n;
         int c[K];
         bool bad = false;
         #pragma unroll
         for (int t = 0; t < K; ++t) {
-            const int sn = combos[i * K + t];
+            const int sn = live ? combos[(i0 + lane) * K + t] : 0;
             bad |= sn < 0 || sn >= d.M;
             c[t] = sn < 0 || sn >= d.M ? 0 : sn;
         }
-        if (bad) {
-            atomicOr(err, 1);
-            continue;
+        if (bad) atomicOr(err, 1);
+        const unsigned long long keep = __ballot(live && !bad);
+        unsigned acc[C];
+        if constexpr (K < 4) {
+            count_small<K>(d, c, acc);
+        } else {
+            int dig[K > 4 ? K - 4 : 1], x = gi;
+            #pragma unroll
+            for (int t = K - 5; t >= 0; --t) {
+                dig[t] = x % 3;
+                x /= 3;
+            }
+            g3_count<K>(d, c, dig, cl, acc);
         }
-        (void)generic_num<K, true>(d, c, 0, tables + i * (2ull * pow3c(K)), 1);
+        // first word of this part in the group's tables
+        uint32_t *out = tables + i0 * (2ull * pow3c(K)) + (K < 4 ? 0 : cl * pow3c(K) + gi * 81);
+        #pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            __syncthreads();
+            if (lane >> 5 == half) {
+                #pragma unroll
+                for (int x = 0; x < C; ++x) slot[(lane & 31) * ROW + x] = acc[x];
+            }
+            __syncthreads();
+            #pragma unroll 4
+            for (int e = lane; e < 32 * C; e += 64) {
+                const int t = e / C, x = e - t * C, at = 32 * half + t;
+                if ((keep >> at) & 1) out[(unsigned long long)at * (2 * pow3c(K)) + x] = slot[t * ROW + x];
+            }
+        }
     }
 }
 
 // N * MI of a table by Equation 1 from the exact n ln n table, as the scans
 // score a combination, then MI = that / 2^shift / N; a table whose classes do
-// not sum to the dataset's class sizes is rejected.  One lane per table, 64
-// tables per wave: the wave stages kMiChunk cells of both classes of each of
-// its tables into its LDS slot (each class's cells read as consecutive
-// words), then every lane sums its own table's terms from there.  With LDT
-// the n ln n table (n = 0 .. N) is staged at LDS address 0 first.
-constexpr int kMiChunk = 16;
-constexpr int kMiRow = 2 * kMiChunk + 1;  // words per table in a slot; the odd stride keeps lanes on distinct banks
+// not sum to the dataset's class sizes is rejected.  LANES lanes per table,
+// neighbouring cells in neighbouring lanes, BATCH cells a lane loaded at
+// once; their sums (integers, so in any order) meet in a butterfly.  With LDT
+// the n ln n table (n = 0 .. N) is staged at LDS address 0 first.  Bound by
+// the latency of a wave's loads and look-ups: 100000 tables of order 4, N =
+// 2048: 82 us with a table per lane staged in LDS (1563 waves), now 24.
+//
+// Lanes per table, and cells a lane: as few as hold a table of order 2 or 3
+// (a million tables of order 2, N = 128, counted and scored: 107 us, with 16
+// lanes a table 196).
+constexpr int mi_lanes(int order) { return order == 2 ? 4 : (order == 3 ? 8 : (order <= 5 ? 16 : 64)); }
+constexpr int mi_batch(int order) { return order == 2 ? 3 : (order == 3 ? 4 : 6); }
 
-template <bool LDT>
+template <int LANES, int BATCH, bool LDT>
 __global__ void __launch_bounds__(256) mi_kernel(DsView d, int P, long long score_const,
                                                  const uint32_t *__restrict__ tables, unsigned long long n,
                                                  double *__restrict__ mi, int *__restrict__ err) {
-    // dynamic LDS: [LDT: 2 (N + 1) words of n ln n table][4 waves x 64 x kMiRow words of staged cells]
-    extern __shared__ __attribute__((aligned(16))) unsigned char s_mi[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_mi[];  // LDT: 2 (N + 1) words
     unsigned *s_t = (unsigned *)s_mi;
-    const int tl_words = LDT ? (2 * (d.N + 1) + 3) & ~3 : 0;
-    unsigned *slot = s_t + tl_words + (threadIdx.x >> 6) * (64 * kMiRow);
     bool at0 = false;  // the lookups address the staged table from LDS address 0
     if constexpr (LDT) {
         const unsigned *src = (const unsigned *)d.tlog;
@@ -3597,45 +3672,45 @@ __global__ void __launch_bounds__(256) mi_kernel(DsView d, int P, long long scor
         __syncthreads();
         at0 = (unsigned)(uintptr_t)(lu32 *)s_t == 0u;
     }
-    const int lane = threadIdx.x & 63;
-    const unsigned long long groups = (n + 63) / 64;
-    const unsigned long long n_waves = (unsigned long long)gridDim.x * 4;
-    for (unsigned long long g = blockIdx.x * 4ull + (threadIdx.x >> 6); g < groups; g += n_waves) {
-        const unsigned long long i0 = g * 64;
-        const int nt = (int)min(64ull, n - i0);
-        long long num = score_const;
+    const int sub = threadIdx.x % LANES;
+    const unsigned n_case = (unsigned)d.ncls[0], n_ctrl = (unsigned)d.ncls[1];
+    for (unsigned long long i = (blockIdx.x * 256ull + threadIdx.x) / LANES; i < n;
+         i += gridDim.x * (256ull / LANES)) {
+        const uint32_t *T = tables + i * 2ull * (unsigned)P;
+        long long num = 0;
         unsigned long long s0 = 0, s1 = 0;
         bool ok = true;
-        for (int c0 = 0; c0 < P; c0 += kMiChunk) {
-            const int cw = min(kMiChunk, P - c0), row = 2 * cw;
-            for (int j = lane; j < nt * row; j += 64) {
-                const int t = j / row, r = j - t * row, cl = r >= cw ? 1 : 0, x = r - cl * cw;
-                slot[t * kMiRow + cl * kMiChunk + x] =
-                    tables[(i0 + t) * 2ull * (unsigned)P + (unsigned)(cl * P + c0 + x)];
+        for (int x0 = sub; x0 < P; x0 += LANES * BATCH) {
+            unsigned n0[BATCH], n1[BATCH];
+            #pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int x = x0 + u * LANES;
+                n0[u] = x < P ? T[x] : 0u;
+                n1[u] = x < P ? T[P + x] : 0u;
             }
-            wave_sync();
-            if (lane < nt) {
-                for (int x = 0; x < cw; ++x) {
-                    const unsigned n0 = slot[lane * kMiRow + x], n1 = slot[lane * kMiRow + kMiChunk + x];
-                    const bool in = n0 <= (unsigned)d.ncls[0] && n1 <= (unsigned)d.ncls[1];
-                    ok &= in;
-                    s0 += n0;
-                    s1 += n1;
-                    num += in ? (LDT && at0 ? cell_term_lds(n0, n1) : cell_term_counted(d.tlog, n0, n1)) : 0;
-                }
+            #pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const bool in = n0[u] <= n_case && n1[u] <= n_ctrl;
+                ok &= in;
+                s0 += n0[u];
+                s1 += n1[u];
+                const unsigned a = in ? n0[u] : 0u, b = in ? n1[u] : 0u;  // (an empty cell's term is 0)
+                num += LDT && at0 ? cell_term_lds(a, b) : cell_term_counted(d.tlog, a, b);
             }
-            wave_sync();
         }
-        if (lane < nt) {
-            ok &= s0 == (unsigned long long)d.ncls[0] && s1 == (unsigned long long)d.ncls[1];
-            mi[i0 + lane] = ok ? ldexp((double)num, -d.shift) / (double)d.N : __builtin_nan("");
+        #pragma unroll
+        for (int off = LANES / 2; off > 0; off >>= 1) {
+            num += (long long)__shfl_xor((unsigned long long)num, off, LANES);
+            s0 += __shfl_xor(s0, off, LANES);
+            s1 += __shfl_xor(s1, off, LANES);
+            ok &= __shfl_xor((int)ok, off, LANES) != 0;
+        }
+        if (sub == 0) {
+            ok &= s0 == (unsigned long long)n_case && s1 == (unsigned long long)n_ctrl;
+            mi[i] = ok ? ldexp((double)(score_const + num), -d.shift) / (double)d.N : __builtin_nan("");
             if (!ok) atomicOr(err, 1);
         }
     }
-}
-
-size_t mi_lds_bytes(int N, bool ldt) {
-    return (ldt ? (size_t)4 * ((2 * (N + 1) + 3) & ~3) : 0) + (size_t)4 * 4 * 64 * kMiRow;
 }
 
 template <int K>
@@ -3645,7 +3720,11 @@ static hipError_t launch_function_k(int fn, hipStream_t st, const DsView &d, con
         hipLaunchKernelGGL(gt_kernel<K>, dim3(grid), dim3(256), 0, st, d, combos, n, (uint32_t *)out, err);
     } else {
         if constexpr (K < 2) return hipErrorInvalidValue;  // tables start at order 2
-        else hipLaunchKernelGGL(ct_kernel<K>, dim3(grid), dim3(256), 0, st, d, combos, n, (uint32_t *)out, err);
+        else {
+            const unsigned long long units = (n + 63) / 64 * ct_units<K>();
+            hipLaunchKernelGGL(ct_kernel<K>, dim3((unsigned)(units < (1u << 20) ? units : 1u << 20)), dim3(64), 0, st, d,
+                               combos, n, (uint32_t *)out, err);
+        }
     }
     return hipGetLastError();
 }
@@ -3655,12 +3734,22 @@ hipError_t launch_function(int fn, int order, hipStream_t st, const DsView &d, c
                            long long score_const) {
     if (fn == 2) {
         // the exact table in LDS when it fits beside two workgroups per CU
-        if ((size_t)8 * (d.N + 1) <= 64 * 1024)
-            hipLaunchKernelGGL(mi_kernel<true>, dim3(grid), dim3(256), mi_lds_bytes(d.N, true), st, d, pow3i(order),
-                               score_const, tables, n, (double *)out, err);
-        else
-            hipLaunchKernelGGL(mi_kernel<false>, dim3(grid), dim3(256), mi_lds_bytes(d.N, false), st, d,
-                               pow3i(order), score_const, tables, n, (double *)out, err);
+        const size_t tl = (size_t)8 * (d.N + 1);
+        const bool ldt = tl <= 64 * 1024;
+        auto pick = [&](auto oc) {
+            constexpr int L = mi_lanes(oc.value), B = mi_batch(oc.value);
+            return ldt ? mi_kernel<L, B, true> : mi_kernel<L, B, false>;
+        };
+        auto *fn2 = order == 2   ? pick(std::integral_constant<int, 2>{})
+                    : order == 3 ? pick(std::integral_constant<int, 3>{})
+                    : order <= 5 ? pick(std::integral_constant<int, 5>{})
+                                 : pick(std::integral_constant<int, 8>{});
+        // as many workgroups as a CU holds at once (each stages the table)
+        const unsigned long long want = (n * (unsigned)mi_lanes(order) + 255) / 256;
+        const size_t per_cu = ldt ? (size_t)160 * 1024 / tl : 8;
+        grid = (int)(want < (unsigned long long)grid * (per_cu < 8 ? per_cu : 8) ? want : grid * (per_cu < 8 ? per_cu : 8));
+        hipLaunchKernelGGL(fn2, dim3(grid), dim3(256), ldt ? tl : 0, st, d, pow3i(order), score_const, tables, n,
+                           (double *)out, err);
         return hipGetLastError();
     }
     switch (order) {

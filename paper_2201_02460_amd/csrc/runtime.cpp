@@ -2121,10 +2121,9 @@ static int run_function(epi_ctx *ctx, int fn, int32_t dataset_id, int32_t order,
     if (n == 0) return EPI_OK;
     if (!d_out || (fn < 2 && !d_combos) || (fn == 2 && !d_tables)) return fail(EPI_EINVAL, "null buffer");
     const unsigned long long words = (unsigned long long)(d->w4[0] + d->w4[1]) * 4;
-    const unsigned long long threads = fn == 0 ? n * words * (order >= 5 ? 9 : 1) : n;
-    const unsigned long long want = (threads + 255) / 256;
-    // MI stages its n ln n table per workgroup: fewer, longer-lived workgroups
-    const int grid = (int)std::min<unsigned long long>(want, (unsigned long long)C->n_cu * (fn == 2 ? 8 : 64));
+    const unsigned long long want = (n * words * (order >= 5 ? 9 : 1) + 255) / 256;
+    // genotype rows: up to 64 workgroups a CU; MI sizes its launch from the CUs
+    const int grid = fn == 2 ? C->n_cu : (int)std::min<unsigned long long>(want, (unsigned long long)C->n_cu * 64);
     void *d_err = nullptr;
     int rc = C->alloc.alloc(256, &d_err);
     if (rc) return rc;
