@@ -344,10 +344,10 @@ int epi_batch_destroy(epi_ctx *ctx, int32_t batch_id);
  * order 3 blocks 1, 2, 4, 8, EPI_BLOCK_MFMA_FP4 and EPI_BLOCK_MFMA_FP4_2J;
  * order 4 the reduced-cell
  * kernel (reported as 0), EPI_BLOCK_ALL_CELLS and EPI_BLOCK_SEGMENTED;
- * orders 5-8 EPI_BLOCK_ALL_CELLS and EPI_BLOCK_SEGMENTED.  Each is timed on
- * eight slices of work items spread evenly over the whole scan (each about
- * 8 items per wave of the launch, or an eighth of the scan if that is less)
- * and its time divided by the
+ * orders 5-8 EPI_BLOCK_ALL_CELLS and EPI_BLOCK_SEGMENTED.  Each is timed as
+ * a scan runs it, pilot pass and all: whole where the scan has at most 64
+ * work items per wave of the launch, else on eight slices of 8 items per wave
+ * spread evenly over it, its time divided by the
  * combinations those items score (counted on the host), so kernels whose
  * items hold different numbers of combinations compare fairly.  The choice
  * is also written to the cache file named by EPI_TUNE_CACHE (if set).  Scans

@@ -1283,7 +1283,7 @@ static int plan_enqueue(Ctx *c, Plan *p, hipStream_t st, bool timing, unsigned l
         ++q;
         if (timing && single) HIPCHK(hipEventRecord(p->ev[2], st));
         for (auto &g : p->groups) {
-            if (g.pilot_total > 0 && item_cap == ~0ull)
+            if (g.pilot_total > 0)
                 HIPCHK(launch_pilot(g.np2, g.np3, g.gk, (int)std::min<unsigned long long>(g.grid, g.pilot_total / 4), st,
                                     tasks + g.task_off, (int)g.scans.size(), g.pilot_total, c->d_binom, c->bstride,
                                     g.tab_cap, g.kmax, g.stage_cap));
@@ -1321,10 +1321,13 @@ static int plan_enqueue(Ctx *c, Plan *p, hipStream_t st, bool timing, unsigned l
                 HIPCHK(launch_init_counters(st, p->d_queues, 1, nullptr, nullptr, 0, nullptr));
             }
             if (timing && single) HIPCHK(hipEventRecord(p->ev[2], st));
-            if (s.pilot_n > 0 && item_cap == ~0ull)
+            if (s.pilot_n > 0)
                 HIPCHK(launch_pilot(g.np2, g.np3, g.gk, std::min(g.grid, s.pilot_n / 4), st, tasks + i, 1,
                                     (unsigned long long)s.pilot_n, c->d_binom, c->bstride, g.tab_cap, g.kmax,
                                     g.stage_cap));
+            // (the tuner's slices: the pilot pass spans the whole scan and is
+            // timed apart, ev[2] to ev[1])
+            if (timing && single && item_cap != ~0ull) HIPCHK(hipEventRecord(p->ev[1], st));
             HIPCHK(launch_scan(g.np2, g.np3, g.gk, g.grid, st, tasks + i, 1, std::min(s.n_items, item_cap),
                                p->d_queues + 1, c->d_binom, c->bstride, g.tab_cap, g.kmax, g.stage_cap, p->check));
             HIPCHK(launch_init_counters(st, p->d_queues + 1, 1, nullptr, nullptr, 0, nullptr));
@@ -1562,12 +1565,16 @@ static std::vector<int> tune_candidates(const Dataset *ds, int order) {
     return v;
 }
 
-// Time each candidate kernel on slices spread over the whole work-item space
-// of the dataset's own scan (kSlices contiguous runs at evenly spaced
-// starts, each about 8 items per wave of its launch, so the launch's start
-// and drain do not decide), normalised by the combinations those items score
-// (counted on the host from the items), and keep the fastest per (order,
-// size bucket).
+// Time each candidate kernel as a scan runs it and keep the fastest per
+// (order, size bucket).  A scan of up to kSlices x 8 work items per wave of
+// its launch is timed whole, with its pilot pass.  Of a larger one, slices
+// spread over the whole work-item space (kSlices contiguous runs at evenly
+// spaced starts, each 8 items per wave, so the launch's start and drain do
+// not decide) are timed from the bound of the scan's pilot pass, normalised by
+// the combinations their items score (counted on the host from the items),
+// and the pilot pass by those of the whole scan.  (In slices without the pilot
+// pass, order 3, M = 151, N = 1237 took 1.9 ns a combination on block 16 and
+// 1.3 on block 1, which was chosen; a scan takes 0.16 and 1.24.)
 int autotune(Ctx *c, int ds_id, int order, int *choice) {
     constexpr int kSlices = 8;
     Dataset *ds;
@@ -1587,29 +1594,25 @@ int autotune(Ctx *c, int ds_id, int order, int *choice) {
         if (rc) return rc;
         const PlanScan &s = p->scans[0];
         const unsigned long long total = s.n_items;
-        const unsigned long long len = std::max<unsigned long long>(
-            1, std::min<unsigned long long>(total / kSlices, (unsigned long long)p->groups[0].grid * 4 * 8));
+        const unsigned long long len = (unsigned long long)p->groups[0].grid * 4 * 8;
+        const bool whole = total <= kSlices * len;
         Task *staged = (Task *)((char *)p->h_stage + p->stage_layout_bytes);
-        // slices are timed without the pilot pass (its items span the task)
-        p->scans[0].pilot_n = 0;
-        staged[0].pilot_n = 0;
-        staged[0].pilot_first = 0;
         double best_rep = 1e30;
         for (int rep = 0; rep < 3 && !rc; ++rep) {
-            double ms_sum = 0;
+            double ms_sum = 0, pilot_ms = 0;
             unsigned long long valid = 0;
-            for (int k = 0; k < kSlices && !rc; ++k) {
-                const unsigned long long first = total > len ? (total - len) * (unsigned long long)k / (kSlices - 1) : 0;
-                const unsigned long long n = std::min(len, total - first);
+            for (int k = 0; k < (whole ? 1 : kSlices) && !rc; ++k) {
+                const unsigned long long first = whole ? 0 : (total - len) * (unsigned long long)k / (kSlices - 1);
                 staged[0].first_item = first;
-                rc = plan_run(c, p, c->stream, n);
+                rc = plan_run(c, p, c->stream, whole ? ~0ull : len);
                 if (!rc) rc = plan_wait(p);
-                float ms = 0;
-                if (!rc && hipEventElapsedTime(&ms, p->ev[2], p->ev[3]) == hipSuccess) ms_sum += ms;
-                valid += valid_in_items(s, first, first + n);
-                if (total <= len) break;
+                float ms = 0, pms = 0;
+                if (!rc && hipEventElapsedTime(&ms, p->ev[whole ? 2 : 1], p->ev[3]) == hipSuccess) ms_sum += ms;
+                if (!rc && !whole && hipEventElapsedTime(&pms, p->ev[2], p->ev[1]) == hipSuccess) pilot_ms += pms / kSlices;
+                valid += whole ? s.n_combos : valid_in_items(s, first, first + len);
             }
-            if (!rc && rep > 0 && valid) best_rep = std::min(best_rep, ms_sum * 1e6 / (double)valid);
+            if (!rc && rep > 0 && valid)
+                best_rep = std::min(best_rep, ms_sum * 1e6 / (double)valid + pilot_ms * 1e6 / (double)s.n_combos);
         }
         plan_free(c, p);
         delete p;
