@@ -322,17 +322,18 @@ int epi_batch_destroy(epi_ctx *ctx, int32_t batch_id);
  * choice for the order.  Served requests (epi_server_*) always use the fused
  * kernels. */
 #define EPI_BLOCK_SEGMENTED 64
-/* Orders 4-8: all 3^order cells of a combination's table counted.  It is the
- * built-in choice from order 5 on, as 0/1 matrix products of the cell rows of
- * the combination's first SNPs (orders 5-6: three, 7-8: four) and of the
- * others on the matrix cores (variant 8), where n_cases + 2^T n_controls <
- * 2^24, T = the bit width of the case count (up to 4095 individuals per
- * class), N <= 16385 and the cell rows of all pairs take at most 1 GiB and fit
- * the context's budget; else, and at order 4, the per-combination kernel with
- * AND + popcount (Section 2.2 as written).  Order 4 uses the reduced-cell kernel
- * (the cells with genotypes 0 and 1 counted, the others by
- * inclusion-exclusion from the pair and triplet sub-tables) when its
- * triplet sub-table fits, and this block pins the all-cell kernel instead. */
+/* Orders 4-8: the per-combination kernel that counts all 3^order cells of a
+ * combination's table with AND + popcount (Section 2.2 as written).  Order 4
+ * otherwise uses the reduced-cell kernel (the cells with genotypes 0 and 1
+ * counted, the others by inclusion-exclusion from the pair and triplet
+ * sub-tables) when its triplet sub-table fits.  Orders 5-8 otherwise count all
+ * cells as 0/1 matrix products of the cell rows of the combination's first
+ * SNPs (orders 5-6: three, 7-8: four) and of the others on the matrix cores
+ * (variant 8), where n_cases + 2^T n_controls < 2^24, T = the bit width of the
+ * case count (up to 4095 individuals per class), N <= 16385, M <= 4096, the
+ * scan has at most 2^30 products of 27 x 27 cell rows (27 combinations of
+ * order 5, 9 of order 6, 3 of order 7 or one of order 8 each), and the cell
+ * rows of all pairs take at most 1 GiB and fit the context's budget. */
 #define EPI_BLOCK_ALL_CELLS 81
 
 /* Time every counting kernel of `order` on the dataset's own scan and
@@ -342,12 +343,13 @@ int epi_batch_destroy(epi_ctx *ctx, int32_t batch_id);
  * The candidates are the blocks listed above: order 2 prefix blocks 2, 4, 8
  * and EPI_BLOCK_MFMA_FP4;
  * order 3 blocks 1, 2, 4, 8, EPI_BLOCK_MFMA_FP4 and EPI_BLOCK_MFMA_FP4_2J;
- * order 4 the reduced-cell
- * kernel (reported as 0), EPI_BLOCK_ALL_CELLS and EPI_BLOCK_SEGMENTED;
- * orders 5-8 EPI_BLOCK_ALL_CELLS and EPI_BLOCK_SEGMENTED.  Each is timed as
- * a scan runs it, pilot pass and all: whole where the scan has at most 64
- * work items per wave of the launch, else on eight slices of 8 items per wave
- * spread evenly over it, its time divided by the
+ * order 4 the reduced-cell kernel (reported as 0), EPI_BLOCK_ALL_CELLS and
+ * EPI_BLOCK_SEGMENTED;
+ * orders 5-8 EPI_BLOCK_ALL_CELLS (the faster of the matrix-core and the
+ * popcount kernel, and scans then use that one) and EPI_BLOCK_SEGMENTED.
+ * Each is timed as a scan runs it, pilot pass and all: whole where the scan
+ * has at most 64 work items per wave of the launch, else on eight slices of 8
+ * items per wave spread evenly over it, its time divided by the
  * combinations those items score (counted on the host), so kernels whose
  * items hold different numbers of combinations compare fairly.  The choice
  * is also written to the cache file named by EPI_TUNE_CACHE (if set).  Scans
@@ -367,7 +369,8 @@ int epi_autotune_report(epi_ctx *ctx, int32_t dataset_id, int32_t order, int32_t
 /* Pin the counting kernel for `order` on datasets of the same bucket as
  * `dataset_id`, as if the autotuner had chosen `block` (one of the blocks
  * listed above; orders above 3 take EPI_BLOCK_SEGMENTED, EPI_BLOCK_ALL_CELLS
- * and 0).  EPI_BLOCK_MFMA_I8 builds the dataset's integer
+ * and 0; EPI_BLOCK_ALL_CELLS is the popcount kernel at every order from 4 up).
+ * EPI_BLOCK_MFMA_I8 builds the dataset's integer
  * operand copies on the context stream and waits for them (no other work on
  * the dataset may be in flight).  EPI_EINVAL for a block not listed for the
  * order, EPI_EUNSUPPORTED for a matrix-core block on a dataset with 2^22

@@ -869,6 +869,12 @@ static bool x_fits(const Dataset *d, int order) {
            binom_u64(d->M, order) / (unsigned long long)(xna(order) * xnb(order)) < lim / 2;
 }
 
+// ... unless the popcount kernel is pinned for the dataset's size bucket.
+static bool use_x(Ctx *c, int order, const Dataset *d, int force_np) {
+    if (!x_fits(d, order) || force_np == EPI_BLOCK_ALL_CELLS) return false;
+    return force_np == kForceCrossCells || tuned_np_lookup(c, order, d) != EPI_BLOCK_ALL_CELLS;
+}
+
 // Units per work item: about 16 items per wave of a full launch.
 static int x_units_per_item(Ctx *c, int order, unsigned long long n_combos) {
     const unsigned long long units = n_combos / (unsigned long long)(xna(order) * xnb(order));
@@ -933,7 +939,7 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
                 if ((rc = plan_items(c, p.get(), kXGk + 4, s.ds->M, 0, &s.items, &s.n_items))) return cleanup(rc);
                 continue;
             }
-            if (x_fits(s.ds, o) && (!arena || x_bytes(s.ds) <= arena->cap / 2)) {
+            if (use_x(c, o, s.ds, force_np) && (!arena || x_bytes(s.ds) <= arena->cap / 2)) {
                 // without room for its operand rows the scan takes the
                 // per-combination kernel
                 if (plan_alloc(c, p.get(), x_bytes(s.ds), &s.xrows) == EPI_OK) {
@@ -1542,8 +1548,9 @@ static unsigned long long valid_in_items(const PlanScan &s, unsigned long long a
 }
 
 // Candidate kernels of an order, by the block that pins them (order 4:
-// kForceReducedCells for the reduced-cell kernel, which epi_set_prefix_block
-// calls 0).
+// kForceReducedCells for the reduced-cell kernel, orders 5-8:
+// kForceCrossCells for the matrix-core one, which epi_set_prefix_block calls
+// 0).
 static std::vector<int> tune_candidates(const Dataset *ds, int order) {
     if (order == 2) {
         std::vector<int> v{2, 4, 8};
@@ -1560,6 +1567,7 @@ static std::vector<int> tune_candidates(const Dataset *ds, int order) {
     }
     std::vector<int> v;
     if (order == 4 && r4_fits(ds)) v.push_back(kForceReducedCells);
+    if (x_fits(ds, order)) v.push_back(kForceCrossCells);
     v.push_back(EPI_BLOCK_ALL_CELLS);
     v.push_back(EPI_BLOCK_SEGMENTED);
     return v;
@@ -1585,6 +1593,10 @@ int autotune(Ctx *c, int ds_id, int order, int *choice) {
         if (rc) return rc;
     }
     const std::vector<int> cands = tune_candidates(ds, order);
+    auto reported = [&](int blk) {
+        if (order == 4 && blk == kForceReducedCells) return 0;
+        return order >= 5 && blk == kForceCrossCells ? EPI_BLOCK_ALL_CELLS : blk;
+    };
     std::vector<std::pair<int, double>> report;
     double best_t = 1e30;
     int best = cands[0];
@@ -1617,7 +1629,12 @@ int autotune(Ctx *c, int ds_id, int order, int *choice) {
         plan_free(c, p);
         delete p;
         if (rc) return rc;
-        report.emplace_back(order >= 4 && blk == kForceReducedCells ? 0 : blk, best_rep);
+        // the kernels that count all cells of orders 5-8 are one entry, the
+        // faster one's time
+        if (order >= 5 && blk == EPI_BLOCK_ALL_CELLS && !report.empty())
+            report[0].second = std::min(report[0].second, best_rep);
+        else
+            report.emplace_back(reported(blk), best_rep);
         if (best_rep < best_t) {
             best_t = best_rep;
             best = blk;
@@ -1629,11 +1646,12 @@ int autotune(Ctx *c, int ds_id, int order, int *choice) {
         c->seg_pins.erase(key);
         c->tuned.erase(key);
         if (best == EPI_BLOCK_SEGMENTED) c->seg_pins[key] = 1;
-        else if (order <= 3 || (order == 4 && best == EPI_BLOCK_ALL_CELLS && r4_fits(ds))) c->tuned[key] = best;
+        else if (order <= 3 || (best == EPI_BLOCK_ALL_CELLS && (order == 4 ? r4_fits(ds) : x_fits(ds, order))))
+            c->tuned[key] = best;
         c->tune_report[key] = report;
         save_tune_cache(c);
     }
-    *choice = order >= 4 && best == kForceReducedCells ? 0 : best;
+    *choice = reported(best);
     return EPI_OK;
 }
 

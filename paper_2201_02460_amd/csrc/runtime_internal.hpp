@@ -22,9 +22,10 @@ namespace epi {
 constexpr int kBinomN = 65537;     // binomial table columns (n = 0 .. 65536)
 constexpr int kGenRanksHost = 4;   // ranks per lane of the per-combination kernel
 constexpr size_t kScratchBytes = EPI_NOALLOC_SCRATCH_BYTES;  // scratch array of allocation-free scans
-// plan_build's forced kernel for order 4: the reduced-cell kernel (the
-// blocks of the C ABI select the others)
+// plan_build's forced kernels: order 4 by reduced cells, orders 5-8 on the
+// matrix cores (the blocks of the C ABI select the others)
 constexpr int kForceReducedCells = 1;
+constexpr int kForceCrossCells = 2;
 
 int fail(int code, const char *fmt, ...);
 void clear_error();
