@@ -333,7 +333,8 @@ int epi_batch_destroy(epi_ctx *ctx, int32_t batch_id);
  * case count (up to 4095 individuals per class), N <= 16385, M <= 4096, the
  * scan has at most 2^30 products of 27 x 27 cell rows (27 combinations of
  * order 5, 9 of order 6, 3 of order 7 or one of order 8 each), and the cell
- * rows of all pairs take at most 1 GiB and fit the context's budget. */
+ * rows of all pairs take at most 1 GiB and half of what is free of the
+ * context's budget. */
 #define EPI_BLOCK_ALL_CELLS 81
 
 /* Time every counting kernel of `order` on the dataset's own scan and

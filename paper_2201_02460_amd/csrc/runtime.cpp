@@ -103,6 +103,11 @@ void DevAlloc::release(void *p) {
     live.erase(it);
 }
 
+uint64_t DevAlloc::room() {
+    std::lock_guard<std::mutex> g(mu);
+    return budget > used ? budget - used : 0;
+}
+
 void DevAlloc::trim_locked() {
     for (auto &kv : free_) (void)hipFree(kv.second);
     free_.clear();
@@ -591,9 +596,9 @@ void plan_free(Ctx *c, Plan *p) {
         c->alloc.release(s.pairs);
         c->alloc.release(s.triples);
         c->alloc.release(s.seg);
-        c->alloc.release(s.xrows);
         c->alloc.release(s.cand);
     }
+    for (auto &r : p->rows) c->alloc.release(r.d);
     c->alloc.release(p->d_parts);
     c->alloc.release(p->d_tasks);
     c->alloc.release(p->d_counters);
@@ -885,8 +890,24 @@ static bool needs_pairs(const PlanScan &s) {
     return s.variant != kSeg && (s.desc.order == 3 || is_r4(s.variant));
 }
 
-int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool graph, Plan **out,
-               int force_np, bool check, const PlanArena *arena) {
+// The plan's cell rows of a dataset (null: they would take more than half of
+// the room that is left, which the plan's other buffers and later calls need).
+static void *plan_rows(Ctx *c, Plan *p, const Dataset *d) {
+    for (auto &r : p->rows)
+        if (r.ds == d) return r.d;
+    const unsigned long long bytes = x_bytes(d), room = p->arena ? p->arena_cap : c->alloc.room();
+    void *rows = nullptr;
+    if (bytes > room / 2 || plan_alloc(c, p, bytes, &rows) != EPI_OK) {
+        clear_error();
+        return nullptr;
+    }
+    p->rows.push_back(Plan::CellRows{d, rows});
+    return rows;
+}
+
+// matrix: orders 4-8 may take their matrix-core kernels; *took: one did.
+static int plan_try(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool graph, Plan **out, int force_np,
+                    bool check, const PlanArena *arena, bool matrix, bool *took) {
     if (n < 1) return fail(EPI_EINVAL, "empty scan list");
     std::vector<Dataset *> dss(n);
     for (int i = 0; i < n; ++i) {
@@ -934,23 +955,20 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
             else if (force_np != kForceReducedCells) r4 = r4 && use_r4(c, s.ds);
             s.variant = r4 ? kR4 : kGeneric;
             s.np = kGenRanksHost;
-            if (r4 && r4m_fits(s.ds)) {
+            if (matrix && r4 && r4m_fits(s.ds)) {
                 s.variant = kR4M;
+                *took = true;
                 if ((rc = plan_items(c, p.get(), kXGk + 4, s.ds->M, 0, &s.items, &s.n_items))) return cleanup(rc);
                 continue;
             }
-            if (use_x(c, o, s.ds, force_np) && (!arena || x_bytes(s.ds) <= arena->cap / 2)) {
-                // without room for its operand rows the scan takes the
-                // per-combination kernel
-                if (plan_alloc(c, p.get(), x_bytes(s.ds), &s.xrows) == EPI_OK) {
-                    s.variant = kX;
-                    s.np = x_units_per_item(c, o, s.n_combos);
-                    if ((rc = plan_items(c, p.get(), kXGk + o, s.ds->M, s.np, &s.items, &s.n_items)))
-                        return cleanup(rc);
-                    continue;
-                }
-                clear_error();
-                s.xrows = nullptr;
+            // without room for its cell rows the scan takes the
+            // per-combination kernel
+            if (matrix && use_x(c, o, s.ds, force_np) && (s.xrows = plan_rows(c, p.get(), s.ds))) {
+                s.variant = kX;
+                *took = true;
+                s.np = x_units_per_item(c, o, s.n_combos);
+                if ((rc = plan_items(c, p.get(), kXGk + o, s.ds->M, s.np, &s.items, &s.n_items))) return cleanup(rc);
+                continue;
             }
             s.n_items = (s.n_combos + 64ull * kGenRanksHost - 1) / (64ull * kGenRanksHost);
         }
@@ -1254,6 +1272,19 @@ int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool 
     return EPI_OK;
 }
 
+// A plan that does not fit with the matrix-core kernels of orders 4-8 (their
+// rows, item tables and larger launches) is built without them.
+int plan_build(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, bool graph, Plan **out, int force_np,
+               bool check, const PlanArena *arena) {
+    bool took = false;
+    int rc = plan_try(c, descs, n, persistent, graph, out, force_np, check, arena, true, &took);
+    if (took && (rc == EPI_ENOMEM || (arena && rc == EPI_EUNSUPPORTED))) {
+        clear_error();
+        rc = plan_try(c, descs, n, persistent, graph, out, force_np, check, arena, false, &took);
+    }
+    return rc;
+}
+
 // Enqueue the whole launch sequence of a plan on st.  With timing, events
 // bracket the sub-table pass, the main kernel and the merge/finalize of a
 // single-scan plan.
@@ -1271,11 +1302,10 @@ static int plan_enqueue(Ctx *c, Plan *p, hipStream_t st, bool timing, unsigned l
                               hipMemcpyHostToDevice, st));
     }
     HIPCHK(launch_init_counters(st, p->d_queues, p->n_queues, p->d_cand_count, p->d_thr, nt, p->d_hist));
-    for (auto &sc : p->scans)
-        if (sc.variant == kX) HIPCHK(launch_xrows(st, sc.ds->view, (v4u *)sc.xrows));
     int q = 0;
     const bool single = nt == 1 && !p->persistent;
     if (timing && single) HIPCHK(hipEventRecord(p->ev[1], st));
+    for (auto &r : p->rows) HIPCHK(launch_xrows(st, r.ds->view, (v4u *)r.d));
     if (p->persistent) {
         if (p->n_emit > 0) {
             HIPCHK(launch_scan(4, 0, 0, p->emit_grid, st, tasks + nt, p->n_emit, p->emit_total, p->d_queues + q,

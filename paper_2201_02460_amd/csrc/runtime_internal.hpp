@@ -40,6 +40,7 @@ struct DevAlloc {
     uint64_t used = 0, cached = 0, peak = 0, budget = 0;
     int alloc(size_t bytes, void **out);
     void release(void *p);
+    uint64_t room();  // bytes of the budget not in use
     void trim();
     void trim_locked();
     void destroy();
@@ -77,7 +78,7 @@ struct PlanScan {
     // order 4 by reduced cells: triplet sub-table pass
     void *triples = nullptr;
     int t3_task = -1;
-    void *xrows = nullptr;  // kX: cell rows of the dataset's single SNPs and pairs
+    void *xrows = nullptr;  // kX: the plan's cell rows of the dataset (Plan::rows)
     void *seg = nullptr;  // segmented variant: the launch's per-wave table blocks
     unsigned long long t3_items = 0;
     const void *t3_items_d = nullptr;
@@ -106,6 +107,13 @@ struct Plan {
     int live_scans = 0;
     std::vector<PlanScan> scans;
     std::vector<LaunchGroup> groups;
+    // cell rows of a dataset's single SNPs and pairs, read by all its scans of
+    // the plan on kernel kX
+    struct CellRows {
+        const Dataset *ds;
+        void *d;
+    };
+    std::vector<CellRows> rows;
     int n_emit = 0, emit_grid = 1, emit_stage = 0, n_queues = 0;
     int emit_kmax = 1;  // best-K list entries per wave of the pair-pass launch (order-2 scans scored there)
     constexpr static int kTabMax = 16386;  // screening-table entries that may go to LDS
