@@ -304,10 +304,11 @@ int epi_batch_destroy(epi_ctx *ctx, int32_t batch_id);
  *            4 n_cases + 2^T n_controls < 2^24 (e.g. up to 2047 individuals
  *            per class).
  * Every kernel produces the same integers and therefore the same results.
- * Scans of order 2, of order 3 on the matrix-core blocks and of order 4 by
- * reduced cells first run a pilot pass: up to one work item per wave, from
- * the middle of the scan, whose best screening sums, lowered by the screen's error bound, go
- * into the scan's score histogram; the K-th best of those is a lower bound
+ * Scans of order 2, of order 3 on the matrix-core blocks, of order 4 by
+ * reduced cells and of orders 5-8 on the matrix cores first run a pilot pass:
+ * up to one work item per wave, from the middle of the scan, whose best
+ * screening sums, lowered by the screen's error bound, go into the scan's
+ * score histogram; the K-th best of those is a lower bound
  * of the final K-th best score, which every wave of the scan then starts
  * from (same results, fewer combinations scored exactly while the bound
  * rises). */
@@ -348,9 +349,10 @@ int epi_batch_destroy(epi_ctx *ctx, int32_t batch_id);
  * EPI_BLOCK_SEGMENTED;
  * orders 5-8 EPI_BLOCK_ALL_CELLS (the faster of the matrix-core and the
  * popcount kernel, and scans then use that one) and EPI_BLOCK_SEGMENTED.
- * Each is timed as a scan runs it, pilot pass and all: whole where the scan
- * has at most 64 work items per wave of the launch, else on eight slices of 8
- * items per wave spread evenly over it, its time divided by the
+ * Each is timed as a scan runs it, pilot pass and all: whole where C(M, order)
+ * 3^order N is at most 2.7e13, else on eight slices of work items spread
+ * evenly over the scan (each about 8 items per wave of the launch, or an
+ * eighth of the scan if that is less), its time divided by the
  * combinations those items score (counted on the host), so kernels whose
  * items hold different numbers of combinations compare fairly.  The choice
  * is also written to the cache file named by EPI_TUNE_CACHE (if set).  Scans

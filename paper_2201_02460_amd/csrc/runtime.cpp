@@ -420,10 +420,16 @@ bool seg_pinned(Ctx *c, int order, const Dataset *d) {
 }
 
 // Prefix block of an order-2 scan: the tuned value, else the matrix cores
-// from M = 1000 on and popcount block 4 below.  (us a scan, block 4 / matrix
-// cores: M = 600, N = 500 102 / 133, N = 2000 114 / 139; M = 1000, N = 1000
-// 132 / 112, N = 4000 168 / 125; M = 4000, N = 500 516 / 244, N = 4000 655 /
-// 280: below, the 32 x 32 blocks are too few to fill the device.)
+// from M = 1000 on and popcount block 4 below, where the 32 x 32 blocks are
+// too few to fill the device at some sizes.  us a scan, block 4 / matrix cores:
+//   M     N = 300    4000       8000       15001       17000        40000
+//   500   103 / 125  129 / 144  158 / 234  219 / 258   313 / 246    416 / 296
+//   700   110 / 108  144 / 124  176 / 323  253 / 349   519 / 336    623 / 368
+//   900   121 / 107  154 / 130  193 / 160  268 / 193   711 / 451    796 / 486
+//   1000  132 / 112  175 / 131  212 / 153  297 / 194   866 / 509    1002 / 576
+//   2000  272 / 148  339 / 165  403 / 189  517 / 236   1627 / 1655  1832 / 1715
+//   4000  476 / 237  649 / 276  817 / 324  1356 / 424  2495 / 1790  3748 / 2019
+// (17000 and 40000: no screening table in LDS.)
 int default_np2(Ctx *c, const Dataset *d) {
     const int t = tuned_np_lookup(c, 2, d);
     if (t > 0 && (t != kNpMfma || d->qa)) return t;
@@ -702,15 +708,15 @@ int group_list_cap(int np2, int np3, int gk, int tab_cap, int top_k, int stage_c
                : top_k;
 }
 
-// Whether the dataset can run order-3 block np: the matrix-core blocks need
-// their operand copies, and the two-middle-SNP one its class sizes to fit
-// one float accumulator (q3_pack_fits).
 // The instantiation of a launch group's order-3 block for n datasets, n_pack
 // of them with both classes in one accumulator.
 int np3_group_inst(int np3, int n, int n_pack) {
     return np3 != kNpMfma ? np3 : (n_pack == n ? kNpMfmaP : (n_pack == 0 ? kNpMfmaS : kNpMfma));
 }
 
+// Whether the dataset can run order-3 block np: the matrix-core blocks need
+// their operand copies, and the two-middle-SNP one its class sizes to fit
+// one float accumulator (q3_pack_fits).
 bool np3_usable(const Dataset *d, int np) {
     if (np == kNpMfma) return d->qa != nullptr;
     if (np == kNpMfma2) return d->qa != nullptr && q3_pack_fits(d->n_case, d->n_ctrl);
@@ -831,7 +837,7 @@ static void pick_tab_cap(const Plan *p, LaunchGroup &g) {
 }
 
 // Order 4 by reduced cells needs the dataset's matrix-core operands (for the
-// triplet sub-table pass) and a triplet sub-table of C(M,3) x 64 bytes; larger
+// triplet sub-table pass) and a triplet sub-table of C(M,3) x 32 bytes; larger
 // ones take the per-combination kernel.
 static constexpr unsigned long long kMaxTripleBytes = 8ull << 30;
 // (its cells hold 4 n of each class in 16 bits: classes of at most 16383)
@@ -859,9 +865,11 @@ static bool r4m_fits(const Dataset *d) {
 // Orders 5-8 count all cells on the matrix cores (kX) where both classes fit
 // one float accumulator (x_pack_fits: up to 4095 individuals a class), the
 // screening table fits the LDS, and the cell rows of the pairs take at most
-// 1 GiB with 31-bit group and unit numbers; elsewhere the popcount kernel
-// does.  It is faster at every size tried, down to M = 20, N = 1000 at order
-// 5 (a scan takes 203 us against 501) and M = 14, N = 1000 at order 8.
+// 1 GiB with 31-bit subset ranks and, so that an item's number within its SNP
+// is one too, less than 2^30 units in all (order 5 up to 324 SNPs, 6 to 140, 7
+// to 80, 8 to 54); elsewhere the popcount kernel does.  It is faster at every
+// size tried, down to M = 20, N = 1000 at order 5 (a scan takes 203 us against
+// 501) and M = 14, N = 1000 at order 8.
 static constexpr unsigned long long kMaxRowBytes = 1ull << 30;
 static unsigned long long x_bytes(const Dataset *d) {
     return x_row_bytes(d->M, x_steps(d->n_case, d->n_ctrl));
@@ -1570,7 +1578,10 @@ static unsigned long long valid_in_items(const PlanScan &s, unsigned long long a
                 const long long m0 = j + 1 + mb * 64;
                 n += clip(ib * np, std::min(ib * np + np, j)) * clip(m0, std::min(m0 + 64, M));
             } else {
-                n += clip(ib * 16, std::min(ib * 16 + 16, j)) * clip(std::max(mb * 32, j + 1), std::min(mb * 32 + 32, M));
+                // (two middle SNPs an item: the second adds nothing past its run)
+                for (long long jj = j; jj < j + (kind == kItemsF3M2 ? 2 : 1); ++jj)
+                    n += clip(ib * 16, std::min(ib * 16 + 16, jj)) *
+                         clip(std::max(mb * 32, jj + 1), std::min(mb * 32 + 32, M));
             }
         }
     }
@@ -1603,16 +1614,20 @@ static std::vector<int> tune_candidates(const Dataset *ds, int order) {
     return v;
 }
 
+static constexpr double kTuneWhole = 2.7e13;
+
 // Time each candidate kernel as a scan runs it and keep the fastest per
-// (order, size bucket).  A scan of up to kSlices x 8 work items per wave of
-// its launch is timed whole, with its pilot pass.  Of a larger one, slices
-// spread over the whole work-item space (kSlices contiguous runs at evenly
-// spaced starts, each 8 items per wave, so the launch's start and drain do
-// not decide) are timed from the bound of the scan's pilot pass, normalised by
-// the combinations their items score (counted on the host from the items),
-// and the pilot pass by those of the whole scan.  (In slices without the pilot
-// pass, order 3, M = 151, N = 1237 took 1.9 ns a combination on block 16 and
-// 1.3 on block 1, which was chosen; a scan takes 0.16 and 1.24.)
+// (order, size bucket).  A scan of up to kTuneWhole cells x individuals (order
+// 3: 1.5 times M = 1000, N = 4000) is timed whole, with its pilot pass, by
+// every candidate.  Of a larger one, slices spread over the whole work-item
+// space (kSlices contiguous runs at evenly spaced starts, each about 8 items
+// per wave of its launch) are timed from the bound of the scan's pilot pass,
+// normalised by the combinations their items score (counted on the host from
+// the items), and the pilot pass by those of the whole scan.  Slices are dear
+// and show the start of a scan: order 3, M = 740, N = 1955, blocks 1, 8 and 16
+// take 0.068, 0.061 and 0.0176 ns a combination, in slices 0.56, 0.13 and
+// 0.029.  (Without the pilot pass M = 151, N = 1237 was put at 1.3, 2.4 and 1.9,
+// so block 1 was chosen; a scan takes 1.24, 1.03 and 0.16.)
 int autotune(Ctx *c, int ds_id, int order, int *choice) {
     constexpr int kSlices = 8;
     Dataset *ds;
@@ -1636,21 +1651,24 @@ int autotune(Ctx *c, int ds_id, int order, int *choice) {
         if (rc) return rc;
         const PlanScan &s = p->scans[0];
         const unsigned long long total = s.n_items;
-        const unsigned long long len = (unsigned long long)p->groups[0].grid * 4 * 8;
-        const bool whole = total <= kSlices * len;
+        const unsigned long long len = std::max<unsigned long long>(
+            1, std::min<unsigned long long>(total / kSlices, (unsigned long long)p->groups[0].grid * 4 * 8));
+        const bool whole = (double)s.n_combos * ds->N * pow3i(order) <= kTuneWhole;
         Task *staged = (Task *)((char *)p->h_stage + p->stage_layout_bytes);
         double best_rep = 1e30;
         for (int rep = 0; rep < 3 && !rc; ++rep) {
             double ms_sum = 0, pilot_ms = 0;
             unsigned long long valid = 0;
             for (int k = 0; k < (whole ? 1 : kSlices) && !rc; ++k) {
-                const unsigned long long first = whole ? 0 : (total - len) * (unsigned long long)k / (kSlices - 1);
+                const unsigned long long first =
+                    whole || total <= len ? 0 : (total - len) * (unsigned long long)k / (kSlices - 1);
                 staged[0].first_item = first;
                 rc = plan_run(c, p, c->stream, whole ? ~0ull : len);
                 if (!rc) rc = plan_wait(p);
                 float ms = 0, pms = 0;
                 if (!rc && hipEventElapsedTime(&ms, p->ev[whole ? 2 : 1], p->ev[3]) == hipSuccess) ms_sum += ms;
-                if (!rc && !whole && hipEventElapsedTime(&pms, p->ev[2], p->ev[1]) == hipSuccess) pilot_ms += pms / kSlices;
+                if (!rc && !whole && hipEventElapsedTime(&pms, p->ev[2], p->ev[1]) == hipSuccess)
+                    pilot_ms += pms / kSlices;
                 valid += whole ? s.n_combos : valid_in_items(s, first, first + len);
             }
             if (!rc && rep > 0 && valid)

@@ -35,8 +35,8 @@ def main_ns(cx, ds, order, M, K=16, n=9):
     return sorted(t)[n // 2] * 1e6 / math.comb(M, order)
 
 
-@pytest.mark.parametrize("order,M,N", [(2, 300, 1500), (3, 151, 1237), (3, 90, 3000), (4, 60, 900), (5, 25, 800),
-                                       (7, 16, 600)])
+@pytest.mark.parametrize("order,M,N", [(2, 300, 1500), (3, 151, 1237), (3, 90, 3000), (3, 740, 1955), (4, 60, 900),
+                                       (5, 25, 800), (7, 16, 600)])
 def test_small_scan_tuned_as_it_runs(cx, order, M, N):
     from paper_2201_02460_amd import epi
 
