@@ -260,10 +260,9 @@ struct Task {
                                       //   lowest index), else lexicographic
     unsigned long long *digest;       // checking launches: [0] combinations scored, [1] their digest sum
                                       //   (null: no check)
-    unsigned long long pilot_first;   // order 2, matrix-core order 3, order 4 by reduced cells: items
-    int32_t pilot_n;                  //   pilot_first .. + pilot_n - 1 were counted into the histogram by
-                                      //   the pilot pass (0: none; a multiple of 4, items past the last
-                                      //   one of the task are empty)
+    unsigned long long pilot_first;   // items pilot_first .. + pilot_n - 1 were counted into the histogram
+    int32_t pilot_n;                  //   by the pilot pass (pilot_items_for; 0: none; a multiple of 4,
+                                      //   items past the last one of the task are empty)
     int32_t pilot_lanes;              // pilot items count every lane's best combination, not the wave's
     unsigned long long pilot_base;    // the task's first item in its pilot launch (a multiple of 4)
 };

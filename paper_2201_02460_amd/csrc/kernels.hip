@@ -402,7 +402,7 @@ EPI_DEV void tk_sort(Cand *a, int n) {
 // Candidates wanted by a wave at once past which they go to the list as a
 // batch (appended, then the list sorted and cut back to K) instead of one
 // replacement and rescan each.  BATCH: the kernels whose waves see few
-// combinations each (order 2, no pilot pass on small scans); in the others
+// combinations each (order 2); in the others
 // the extra code costs the scoring loops registers.
 constexpr int kBatchOffer = 8;
 
@@ -3149,13 +3149,15 @@ ScanKernelFn find_scan_kernel_check(int np2, int np3, int gk) {
 }
 #else
 // ---------------------------------------------------------------------------
-// Pilot pass of the matrix-core order-3 and reduced-cell order-4 scans of a
-// launch group, launched before its main launch.  Each task with pilot_n > 0
+// Pilot pass of a launch group's scans (order 2, order 3 on the matrix cores,
+// order 4 by reduced cells, orders 5-8 on the matrix cores), launched before
+// its main launch.  Each task with pilot_n > 0
 // has pilot_n consecutive pilot items (from the middle of its scan, sharing
 // operand blocks in L2 as the main launch's items do), numbered from
 // pilot_base in the pilot launch; a workgroup takes 4 of them (one per wave,
 // never two tasks).  A wave passes over its item counting the best lower
-// bound of its scores into the task's histogram (one count); the last wave of
+// bound of its scores into the task's histogram (one count, or one per lane
+// where the task has few pilot items: pilot_lanes); the last wave of
 // a task reads the bound the histogram gives (the K-th best of lower bounds
 // of distinct combinations is at most the task's final K-th best) and
 // publishes it.  Every wave of the main launch starts from that bound, and
