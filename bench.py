@@ -46,7 +46,7 @@ BLOCK_MFMA_FP4 = 16
 BLOCK_MFMA_I8 = 32
 BLOCK_MFMA_FP4_2J = 48
 MFMA_KERNELS = {
-    BLOCK_MFMA_FP4: ("scan_persistent<0,16,0> (order-3 reduced cells as fp4 0/1 matrix products)", "scan_mfma"),
+    BLOCK_MFMA_FP4: ("scan_persistent<0,17,0> (order-3 reduced cells as fp4 0/1 matrix products, block 16)", "scan_mfma"),
     BLOCK_MFMA_FP4_2J: ("scan_persistent<0,48,0> (fp4 0/1 matrix products, two middle SNPs per item, both classes "
                         "in one accumulator)", "scan_mfma2"),
 }
@@ -216,7 +216,9 @@ def pcie_bench(epi, spec, G, y, steps):
 
 def orders_bench(epi, torch, names, steps):
     """Plain scans of the other named workloads (one per order), for the
-    per-order rate and roofline fraction of their counting kernels."""
+    per-order rate and roofline fraction of their counting kernels (kernel_ms:
+    pilot and main launch; the sub-tables of orders 3-4 and the cell rows of
+    orders 5-8 are in the wall time only)."""
     from synth import make_workload
 
     out = {}

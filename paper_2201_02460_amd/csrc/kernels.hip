@@ -1564,9 +1564,9 @@ EPI_DEV void item_f3m(const Task &t, unsigned long long local, TopK &tk, Cand *l
 // wave, so its screening sum is one wave reduction and its handling uniform.
 // Bound by the sum of the products and of the scoring's vector and LDS work:
 // two waves a SIMD overlap them only in part (products without the scoring
-// 3.0 ms, scoring without the products 1.5, together 4.3 at order 8, M = 23,
+// 3.0 ms, scoring without the products 1.5, together 3.9 at order 8, M = 23,
 // N = 2048, against 18.8 ms for the popcount kernel; order 5, M = 60,
-// N = 2000: 2.0 ms against 6.7).
+// N = 2000: 1.8 ms against 6.7).
 // ---------------------------------------------------------------------------
 constexpr int pow3c(int k) { return k <= 0 ? 1 : 3 * pow3c(k - 1); }
 
@@ -2530,11 +2530,11 @@ EPI_DEV void item_r4(const Task &t, unsigned long long local, TopK &tk, Cand *li
 // marginals come from the sub-tables, whose colex order puts consecutive i in
 // consecutive lanes.
 //
-// Bound by the scoring: 81 cells are 243 reads of the screening table, about
-// 1100 LDS cycles per 64 combinations, and some 850 vector instructions, next
-// to 1100 matrix-core cycles (22 blocks of 96 individuals).  M = 200, N = 2000:
-// 4.95 ms, 1.4 of it without the scoring and 3.5 without the table reads,
-// against 7.5 ms for kR4; 0.73 of the lanes hold a combination.  A table of
+// Bound by the scoring: 81 cells are 243 reads of the screening table.  M =
+// 200, N = 2000: a wave issues 341 LDS, 1346 vector and 57 matrix instructions
+// of 32 cycles per 64 combinations (counters; 0.73 of the lanes hold one), the
+// kernel takes 5.0 ms, 1.4 of it without the scoring and 3.5 without the table
+// reads, against 7.5 ms for kR4.  A table of
 // t(n0) + t(n1) - t(n0 + n1) for small counts, one read a cell, was slower
 // (6.9): equal small counts share one read of the plain table.
 // ---------------------------------------------------------------------------
