@@ -684,10 +684,17 @@ int default_np3(Ctx *c, const Dataset *d) {
 // wave, which large scans reach.  An order-2 scan of few items has little to
 // save, so there the second counting must be short: M = 298 (about 210 items)
 // at N = 4000 takes 166 us without and 156 with, at N = 9483 152 and 162, but
-// M = 600 (780 items) at N = 8000 401 and 171.
-int pilot_items_for(int variant, int np, unsigned long long n_items, int top_k, int N, int tab_cap, int waves) {
-    if (!((variant == kF3 && is_mfma_np(np)) || variant == kR4 || variant == kR4M || variant == kF2 || variant == kX) || tab_cap < N + 1) return 0;
+// M = 600 (780 items) at N = 8000 401 and 171.  A bound that most combinations
+// reach saves nothing at any order: N = 500, K = 256, us a scan without and
+// with: order 2, M = 20 (190 pairs) 274 and 284; order 4, M = 8 (70) 316 and
+// 335; order 6, M = 9 (84) 370 and 390; but K = 100, order 8, M = 11 (165) 465
+// and 414, order 4, M = 12 (495) 249 and 204.
+int pilot_items_for(int variant, int np, unsigned long long n_items, unsigned long long n_combos, int top_k, int N,
+                    int tab_cap, int waves) {
+    const bool has = variant == kF2 || (variant == kF3 && is_mfma_np(np)) || is_r4(variant) || variant == kX;
+    if (!has || tab_cap < N + 1) return 0;
     if (variant == kF2 && n_items <= 256 && N > 6000) return 0;
+    if (2 * n_combos <= 3ull * (unsigned)top_k) return 0;
     const unsigned long long want = std::max<unsigned long long>(n_items / 32, 4ull * std::max(top_k, 1));
     const unsigned long long n = std::min({(unsigned long long)waves, n_items, want});
     return (int)((n + 3) & ~3ull);
@@ -1182,7 +1189,8 @@ static int plan_try(Ctx *c, const epi_scan_desc *descs, int n, bool persistent, 
         s.pilot_n = 0;
         for (const LaunchGroup &g : p->groups)
             if (std::find(g.scans.begin(), g.scans.end(), i) != g.scans.end())
-                s.pilot_n = pilot_items_for(s.variant, s.np, s.n_items, s.desc.top_k, s.ds->N, g.tab_cap, g.grid * 4);
+                s.pilot_n = pilot_items_for(s.variant, s.np, s.n_items, s.n_combos, s.desc.top_k, s.ds->N, g.tab_cap,
+                                            g.grid * 4);
         set_pilot(t, s.pilot_n, s.n_items);
     }
     {

@@ -207,7 +207,8 @@ hipError_t launch_pilot(int np2, int np3, int gk, int grid, hipStream_t st, cons
                         int stage_cap);
 // Pilot items of a task (a multiple of 4; 0: none), when its screening table
 // fits the launch's LDS table (tab_cap entries).
-int pilot_items_for(int variant, int np, unsigned long long n_items, int top_k, int N, int tab_cap, int waves);
+int pilot_items_for(int variant, int np, unsigned long long n_items, unsigned long long n_combos, int top_k, int N,
+                    int tab_cap, int waves);
 void set_pilot(Task &t, int pilot_n, unsigned long long n_items);
 // 4-wave workgroups per CU of a scan kernel instantiation (VGPRs and LDS:
 // screening-table entries, best-K list entries per wave, staged rows).

@@ -160,7 +160,7 @@ static int admit(Server *S, Request *r) {
     if (sub && (rc = get_items(c, kF2, r->ds->M, 4, &r->emit_items, &r->emit_n))) return rc;
     if (r->variant == kR4 && (rc = get_items(c, kF3, r->ds->M, kNpMfma, &r->t3_items, &r->t3_n))) return rc;
     r->cand_cap = (unsigned)((unsigned long long)S->grid_max * 4 * r->desc.top_k + r->desc.top_k + 64);
-    r->pilot_n = pilot_items_for(r->variant, r->np, r->n_items, r->desc.top_k, r->ds->N, Plan::kTabMax,
+    r->pilot_n = pilot_items_for(r->variant, r->np, r->n_items, r->n_combos, r->desc.top_k, r->ds->N, Plan::kTabMax,
                                  S->grid_max * 4);
     r->big_tab = table_lowers_occupancy(r->ds, r->variant, r->np, o, r->desc.top_k);
     const uint64_t pair_bytes = sub ? pair_table_bytes(r->variant, r->ds->M) : 0;
