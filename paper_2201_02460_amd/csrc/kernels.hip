@@ -2882,22 +2882,27 @@ scan_persistent(const Task *__restrict__ tasks, int n_tasks, unsigned long long 
     // Guided self-scheduling, one queue atomic per chunk of 4 x `per` items for
     // the whole workgroup; the chunk shrinks with the remaining work (estimated
     // from the last chunk).  Wave w takes items first + w, first + w + 4, ...
-    // A chunk that runs over several tasks is handed out task by task, so that
-    // every task's dataset has the LDS screening table (the kernels of orders
-    // 4-8 on the matrix cores score from no other).  What is left of it stays
-    // in s_chunk: in registers it cost order 4 (M = 200, N = 2000) 1.9 %.
+    // For the kernels of orders 4-8 on the matrix cores, which score from the
+    // LDS screening table alone, a chunk that runs over several tasks is handed
+    // out task by task, each with its dataset's table; what is left of it stays
+    // in s_chunk (in registers it cost order 4, M = 200, N = 2000 1.9 %).  The
+    // others take the items past the first task without a table: loading one
+    // for them, and the other schedule of their loops that came with it, cost
+    // batches of six small scans 2-4 %.
+    constexpr bool by_task = GK > kXGk;
     const unsigned long long n_waves = (unsigned long long)gridDim.x * 4;
     unsigned long long est = 0;
-    if (threadIdx.x == 0) s_chunk[1] = 0;
+    if (by_task && threadIdx.x == 0) s_chunk[1] = 0;
     #pragma unroll 1
     for (;;) {
         if (threadIdx.x == 0) {
-            unsigned long long c0 = s_chunk[0], n = s_chunk[1];  // what is left of the chunk
+            // by_task: s_chunk holds what is left of the chunk
+            unsigned long long c0 = by_task ? s_chunk[0] : 0, n = by_task ? s_chunk[1] : 0;
             if (n == 0) {
                 unsigned long long per = (total_items - min(est, total_items)) / (2 * n_waves);
                 per = per < 1 ? 1 : (per > 32 ? 32 : per);
                 c0 = atomicAdd(queue, 4 * per);
-                n = min(4 * per, total_items - min(c0, total_items));
+                n = by_task ? min(4 * per, total_items - min(c0, total_items)) : per;
             }
             s_chunk[0] = c0;
             s_chunk[1] = n;
@@ -2905,23 +2910,27 @@ scan_persistent(const Task *__restrict__ tasks, int n_tasks, unsigned long long 
         __syncthreads();
         // values read back from LDS are wave-uniform: keep them in SGPRs
         const unsigned long long first = rfl64(s_chunk[0]);
-        unsigned long long end = first + (unsigned)uni((int)s_chunk[1]);
+        const unsigned long long n = by_task ? (unsigned)uni((int)s_chunk[1]) : rfl64(s_chunk[1]);
         __syncthreads();
         if (first >= total_items) break;
-        // the task's dataset takes the LDS screening table if it fits
+        unsigned long long end = by_task ? first + n : min(first + 4 * n, total_items);
+        if constexpr (!by_task) est = end;
+        // the first task's dataset takes the LDS screening table if it fits
         {
             int lo = 0, hi = n_tasks - 1;
             while (lo < hi) {
                 int mid = (lo + hi + 1) >> 1;
                 if (tasks[mid].item_base <= first) lo = mid; else hi = mid - 1;
             }
-            const unsigned long long all = end;
-            if (lo + 1 < n_tasks) end = min(end, tasks[lo + 1].item_base);
-            if (threadIdx.x == 0) {
-                s_chunk[0] = end;
-                s_chunk[1] = all - end;
+            if constexpr (by_task) {
+                const unsigned long long all = end;
+                if (lo + 1 < n_tasks) end = min(end, tasks[lo + 1].item_base);
+                if (threadIdx.x == 0) {
+                    s_chunk[0] = end;
+                    s_chunk[1] = all - end;
+                }
+                est = end;
             }
-            est = end;
             const Task &T0 = tasks[lo];
             // the screening reads address the table from LDS address 0; the
             // mirrored half too for the kernels in the signed cell form, when
