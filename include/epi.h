@@ -350,15 +350,16 @@ int epi_batch_destroy(epi_ctx *ctx, int32_t batch_id);
  * orders 5-8 EPI_BLOCK_ALL_CELLS (the faster of the matrix-core and the
  * popcount kernel, and scans then use that one) and EPI_BLOCK_SEGMENTED.
  * Each is timed as a scan runs it, pilot pass and all: whole where C(M, order)
- * 3^order N is at most 2.7e13, else on eight slices of work items spread
- * evenly over the scan (each about 8 items per wave of the launch, or an
- * eighth of the scan if that is less), its time divided by the
- * combinations those items score (counted on the host), so kernels whose
- * items hold different numbers of combinations compare fairly.  The choice
- * is also written to the cache file named by EPI_TUNE_CACHE (if set).  Scans
- * (plain, batched and served) use tuned choices automatically; untuned
- * shapes use built-in defaults (order 2: the matrix cores from 1000 SNPs on,
- * else prefix block 4; order 3: the matrix-core kernel where available).  *choice receives the chosen block. */
+ * 3^order N is at most 1.2e14 (from order 4 up 2.7e13), else on slices of work
+ * items spread evenly over the scan (orders 2-3 four of about 32768
+ * combinations per wave of the launch, from order 4 up eight of 8 items, at
+ * most the scan itself).  The time is divided by the combinations those items
+ * score (counted on the host), so kernels whose items hold different numbers
+ * of combinations compare fairly.  The choice is also written to the cache
+ * file named by EPI_TUNE_CACHE (if set).  Scans (plain, batched and served)
+ * use tuned choices automatically; untuned shapes use built-in defaults (order
+ * 2: the matrix cores from 1000 SNPs on, else prefix block 4; order 3: the
+ * matrix-core kernel where available).  *choice receives the chosen block. */
 int epi_autotune(epi_ctx *ctx, int32_t dataset_id, int32_t order, int32_t *choice);
 
 /* The candidates of the last epi_autotune of `order` for the dataset's size

@@ -1622,22 +1622,23 @@ static std::vector<int> tune_candidates(const Dataset *ds, int order) {
     return v;
 }
 
-static constexpr double kTuneWhole = 2.7e13;
-
 // Time each candidate kernel as a scan runs it and keep the fastest per
-// (order, size bucket).  A scan of up to kTuneWhole cells x individuals (order
-// 3: 1.5 times M = 1000, N = 4000) is timed whole, with its pilot pass, by
-// every candidate.  Of a larger one, slices spread over the whole work-item
-// space (kSlices contiguous runs at evenly spaced starts, each about 8 items
-// per wave of its launch) are timed from the bound of the scan's pilot pass,
-// normalised by the combinations their items score (counted on the host from
-// the items), and the pilot pass by those of the whole scan.  Slices are dear
-// and show the start of a scan: order 3, M = 740, N = 1955, blocks 1, 8 and 16
-// take 0.068, 0.061 and 0.0176 ns a combination, in slices 0.56, 0.13 and
-// 0.029.  (Without the pilot pass M = 151, N = 1237 was put at 1.3, 2.4 and 1.9,
-// so block 1 was chosen; a scan takes 1.24, 1.03 and 0.16.)
+// (order, size bucket).  A scan of up to 1.2e14 cells x individuals (order 3:
+// 6.7 times M = 1000, N = 4000; from order 4 up, whose slower kernels take
+// longer for a cell, 2.7e13) is timed whole, with its pilot pass, by every
+// candidate.  Of a larger one, slices spread over the whole work-item space
+// (contiguous runs at evenly spaced starts) are timed from the bound of the
+// scan's pilot pass, normalised by the combinations their items score (counted
+// on the host from the items), and the pilot pass by those of the whole scan.
+// A slice also shows the start and end of its launch, so the candidates of
+// orders 2-3, whose items hold 64 to 1024 combinations, get four long ones of
+// as many combinations.  (In eight slices of 8 items per wave, order 3, M =
+// 740, N = 1955, blocks 1, 8 and 16 were put at 0.56, 0.13 and 0.029 ns a
+// combination; a scan takes 0.068, 0.061 and 0.0176.  Without the pilot pass M
+// = 151, N = 1237 was put at 1.3, 2.4 and 1.9, so block 1 was chosen; a scan
+// takes 1.24, 1.03 and 0.16.)
 int autotune(Ctx *c, int ds_id, int order, int *choice) {
-    constexpr int kSlices = 8;
+    const int n_slices = order <= 3 ? 4 : 8;
     Dataset *ds;
     epi_scan_desc d{ds_id, order, 16, 0};
     {
@@ -1659,28 +1660,32 @@ int autotune(Ctx *c, int ds_id, int order, int *choice) {
         if (rc) return rc;
         const PlanScan &s = p->scans[0];
         const unsigned long long total = s.n_items;
+        // items per wave of a slice: 32768 combinations, from order 4 up 8 items
+        const double per_wave = order <= 3 ? 32768.0 * (double)total / (double)s.n_combos : 8.0;
         const unsigned long long len = std::max<unsigned long long>(
-            1, std::min<unsigned long long>(total / kSlices, (unsigned long long)p->groups[0].grid * 4 * 8));
-        const bool whole = (double)s.n_combos * ds->N * pow3i(order) <= kTuneWhole;
+            1, std::min(total / n_slices, (unsigned long long)(p->groups[0].grid * 4 * per_wave)));
+        const bool whole = (double)s.n_combos * ds->N * pow3i(order) <= (order <= 3 ? 1.2e14 : 2.7e13);
         Task *staged = (Task *)((char *)p->h_stage + p->stage_layout_bytes);
         double best_rep = 1e30;
         for (int rep = 0; rep < 3 && !rc; ++rep) {
             double ms_sum = 0, pilot_ms = 0;
             unsigned long long valid = 0;
-            for (int k = 0; k < (whole ? 1 : kSlices) && !rc; ++k) {
+            for (int k = 0; k < (whole ? 1 : n_slices) && !rc; ++k) {
                 const unsigned long long first =
-                    whole || total <= len ? 0 : (total - len) * (unsigned long long)k / (kSlices - 1);
+                    whole || total <= len ? 0 : (total - len) * (unsigned long long)k / (n_slices - 1);
                 staged[0].first_item = first;
                 rc = plan_run(c, p, c->stream, whole ? ~0ull : len);
                 if (!rc) rc = plan_wait(p);
                 float ms = 0, pms = 0;
                 if (!rc && hipEventElapsedTime(&ms, p->ev[whole ? 2 : 1], p->ev[3]) == hipSuccess) ms_sum += ms;
                 if (!rc && !whole && hipEventElapsedTime(&pms, p->ev[2], p->ev[1]) == hipSuccess)
-                    pilot_ms += pms / kSlices;
+                    pilot_ms += pms / n_slices;
                 valid += whole ? s.n_combos : valid_in_items(s, first, first + len);
             }
-            if (!rc && rep > 0 && valid)
+            // (the first repetition warms up, and is enough where it is long)
+            if (!rc && valid && (rep > 0 || ms_sum >= 10))
                 best_rep = std::min(best_rep, ms_sum * 1e6 / (double)valid + pilot_ms * 1e6 / (double)s.n_combos);
+            if (ms_sum >= 10) break;
         }
         plan_free(c, p);
         delete p;
